@@ -1258,16 +1258,18 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
   if (gw < 1) gw = 1;
   // per-window scratch of one chunk, one set per stream
   struct Scratch {
-    void *part, *cv, *ev, *vec, *a32, *a16h, *a16l;
+    void *part, *cv, *ev, *vec, *a32, *a16h, *a16l, *log;
   };
   const size_t M = 2 * (size_t)w;
   auto scratch = [&](hipStream_t cs, Scratch* x) -> hv_status {
-    const size_t bytes[7] = {(size_t)gw * nblk * M * M * 4, (size_t)gw * w * w * 16, (size_t)gw * w * 8,
+    const size_t bytes[8] = {(size_t)gw * nblk * M * M * 4, (size_t)gw * w * w * 16, (size_t)gw * w * 8,
                              (size_t)gw * w * w * 16, (size_t)gw * mtiles * w * 64 * 4,
-                             (size_t)gw * mtiles * (w / 8) * 64 * 16, (size_t)gw * mtiles * (w / 8) * 64 * 16};
-    void** dst[7] = {&x->part, &x->cv, &x->ev, &x->vec, &x->a32, &x->a16h, &x->a16l};
-    for (int i = 0; i < 7; ++i) {
-      DevBuf& b = ctx->work(cs, 10 + i);
+                             (size_t)gw * mtiles * (w / 8) * 64 * 16, (size_t)gw * mtiles * (w / 8) * 64 * 16,
+                             jacobi_log_bytes(gw, w, kJacobiSweeps)};
+    void** dst[8] = {&x->part, &x->cv, &x->ev, &x->vec, &x->a32, &x->a16h, &x->a16l, &x->log};
+    const int slot[8] = {10, 11, 12, 13, 14, 15, 16, 18};
+    for (int i = 0; i < 8; ++i) {
+      DevBuf& b = ctx->work(cs, slot[i]);
       hv_status e = b.ensure(bytes[i], &ctx->held);
       if (e) return e;
       *dst[i] = b.ptr;
@@ -1330,7 +1332,7 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
         return s;
       if ((s = timed(ctx, "jacobi", st, [&] {
              return launch_jacobi((const double*)x.cv, g_n, w, (double*)x.ev, (double*)x.vec,
-                                  o.offdiag ? o.offdiag + j0 : nullptr, kJacobiSweeps, st);
+                                  o.offdiag ? o.offdiag + j0 : nullptr, kJacobiSweeps, x.log, st);
            })))
         return s;
       const size_t at = (size_t)j0 * frame;

@@ -572,187 +572,13 @@ __global__ void k_gram_reduce(const float* __restrict__ part, int nblk, int W, d
   cov[(jj * W * W + idx) * 2 + 1] = im * cscale;
 }
 
-// ------------------------------------------------------------------ FP64 Jacobi
-// Cyclic Jacobi for a Hermitian W x W matrix, one block per window, with the
-// round-robin (circle) ordering: in each of the W-1 steps of a sweep, W/2
-// disjoint pairs rotate at once, the matrix in independent 2x2 blocks (the
-// column and the row rotation together) and the eigenvector columns in one
-// pass between two barriers.  Pair (p, q) with a = A_pp,
-// d = A_qq, b = A_pq = |b| e^{i phi}: J = [[c, s], [-s e^{-i phi}, c e^{-i phi}]]
-// with t = sgn(th)/(|th| + sqrt(th^2 + 1)), th = (d - a)/(2|b|),
-// c = 1/sqrt(t^2 + 1), s = t c zeroes A_pq in J^H A J.
+// ------------------------------------------------------------------ FP64 complex values
 struct dc {
   double x, y;
 };
 __device__ inline dc dmul(dc a, dc b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ inline dc dadd(dc a, dc b) { return {a.x + b.x, a.y + b.y}; }
-__device__ inline dc dscale(dc a, double s) { return {a.x * s, a.y * s}; }
 __device__ inline dc dconj(dc a) { return {a.x, -a.y}; }
-
-// JT = W^2 / 2 threads per window (one per eigenvector-pair update of a
-// rotation step; the (W/2)^2 matrix blocks take a half or a quarter of
-// them), at most 1024.  A and V sit in LDS with a padded row stride W + 1, so
-// lanes walking down a column spread over the banks.  The
-// rotation parameters use reciprocal square roots: 1/|b| once, then t and
-// c = 1/sqrt(t^2 + 1).
-template <int W>
-constexpr int jacobi_threads() {
-  return W * W / 2 > 1024 ? 1024 : W * W / 2;
-}
-
-template <int W>
-__device__ inline double jacobi_sum(double v, double* red) {
-  constexpr int JT = jacobi_threads<W>();
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  if constexpr (JT <= 64) {
-    return v;
-  } else {
-    if ((tid & 63) == 0) red[tid >> 6] = v;
-    __syncthreads();
-    double r = 0.0;
-#pragma unroll
-    for (int i = 0; i < JT / 64; ++i) r += red[i];
-    __syncthreads();
-    return r;
-  }
-}
-
-template <int W>
-__global__ __launch_bounds__(jacobi_threads<W>()) void k_jacobi(const double* __restrict__ cov,
-                                                                double* __restrict__ evals,
-                                                                double* __restrict__ evecs,
-                                                                double* __restrict__ offdiag, int max_sweeps) {
-  constexpr int JT = jacobi_threads<W>();
-  constexpr int WP = W + 1;  // padded row stride
-  __shared__ dc A[W * WP];
-  __shared__ dc V[W * WP];
-  __shared__ int pp[W / 2], qq[W / 2];
-  __shared__ double rc[W / 2], rs[W / 2];  // c, s
-  __shared__ dc re[W / 2];                  // e^{-i phi}
-  __shared__ double red[JT / 64 > 0 ? JT / 64 : 1];
-  __shared__ int perm[W];
-  const int tid = threadIdx.x;
-  const long jj = blockIdx.x;
-  const dc* src = reinterpret_cast<const dc*>(cov) + jj * W * W;
-  for (int i = tid; i < W * W; i += JT) {
-    const int r = i / W, c = i % W;
-    A[r * WP + c] = src[i];
-    V[r * WP + c] = {r == c ? 1.0 : 0.0, 0.0};
-  }
-  __syncthreads();
-  for (int sweep = 0;; ++sweep) {
-    // convergence: off-diagonal energy relative to the total; at exit the
-    // ratio sqrt(off / total) is reported, so a window that reached the
-    // sweep limit unconverged is visible to the caller
-    double off = 0.0, tot = 0.0;
-    for (int i = tid; i < W * W; i += JT) {
-      const int r = i / W, c = i % W;
-      const dc v = A[r * WP + c];
-      const double m2 = v.x * v.x + v.y * v.y;
-      tot += m2;
-      if (r != c) off += m2;
-    }
-    const double off_all = jacobi_sum<W>(off, red);
-    const double tot_all = jacobi_sum<W>(tot, red);
-    if (!(off_all > 1e-30 * tot_all) || sweep >= max_sweeps) {
-      if (offdiag && tid == 0) offdiag[jj] = tot_all > 0 ? sqrt(off_all / tot_all) : 0.0;
-      break;
-    }
-    for (int step = 0; step < W - 1; ++step) {
-      if (tid < W / 2) {
-        const int k = tid;
-        auto player = [&](int pos) { return pos == 0 ? 0 : 1 + (pos - 1 + step) % (W - 1); };
-        int p = player(k), q = player(W - 1 - k);
-        if (p > q) {
-          int t = p;
-          p = q;
-          q = t;
-        }
-        pp[k] = p;
-        qq[k] = q;
-        const double a = A[p * WP + p].x, d = A[q * WP + q].x;
-        const dc b = A[p * WP + q];
-        const double b2 = b.x * b.x + b.y * b.y;
-        if (b2 == 0.0 || b2 < 1e-300 * (a * a + d * d)) {  // |b| negligible: no rotation
-          rc[k] = 1.0;
-          rs[k] = 0.0;
-          re[k] = {1.0, 0.0};
-        } else {
-          const double inv = rsqrt(b2);  // 1 / |b|
-          const double th = 0.5 * (d - a) * inv;
-          const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-          const double c = rsqrt(t * t + 1.0);
-          rc[k] = c;
-          rs[k] = t * c;
-          re[k] = {b.x * inv, -b.y * inv};  // e^{-i phi}
-        }
-      }
-      __syncthreads();
-      // The step's rotations act on disjoint index pairs that cover 0..W-1,
-      // so A' = J^H A J splits into independent 2x2 blocks: rows {p_i, q_i}
-      // by columns {p_j, q_j} take the column rotation of pair j,
-      //   A[:,p] = c A[:,p] - s e A[:,q],  A[:,q] = s A[:,p] + c e A[:,q],
-      // then the row rotation of pair i,
-      //   A[p,:] = c A[p,:] - s conj(e) A[q,:],  A[q,:] = s A[p,:] + c conj(e) A[q,:],
-      // in registers, with one read and one write of each element.
-      for (int b = tid; b < (W / 2) * (W / 2); b += JT) {
-        const int i = b / (W / 2), j = b % (W / 2);
-        const int pi = pp[i], qi = qq[i], pj = pp[j], qj = qq[j];
-        const double cj = rc[j], sj = rs[j], ci = rc[i], si = rs[i];
-        const dc ej = re[j], eci = dconj(re[i]);
-        const dc a_pp = A[pi * WP + pj], a_pq = A[pi * WP + qj];
-        const dc a_qp = A[qi * WP + pj], a_qq = A[qi * WP + qj];
-        dc t = dmul(ej, a_pq);
-        const dc n_pp = dadd(dscale(a_pp, cj), dscale(t, -sj));
-        const dc n_pq = dadd(dscale(a_pp, sj), dscale(t, cj));
-        t = dmul(ej, a_qq);
-        const dc n_qp = dadd(dscale(a_qp, cj), dscale(t, -sj));
-        const dc n_qq = dadd(dscale(a_qp, sj), dscale(t, cj));
-        t = dmul(eci, n_qp);
-        A[pi * WP + pj] = dadd(dscale(n_pp, ci), dscale(t, -si));
-        A[qi * WP + pj] = dadd(dscale(n_pp, si), dscale(t, ci));
-        t = dmul(eci, n_qq);
-        A[pi * WP + qj] = dadd(dscale(n_pq, ci), dscale(t, -si));
-        A[qi * WP + qj] = dadd(dscale(n_pq, si), dscale(t, ci));
-      }
-      // V = V J: the column rotation of every pair on every row
-      for (int i = tid; i < (W / 2) * W; i += JT) {
-        const int k = i / W, r = i % W;
-        const int p = pp[k], q = qq[k];
-        const double c = rc[k], sn = rs[k];
-        const dc e = re[k];
-        dc vp = V[r * WP + p], vq = V[r * WP + q];
-        dc ev = dmul(e, vq);
-        V[r * WP + p] = dadd(dscale(vp, c), dscale(ev, -sn));
-        V[r * WP + q] = dadd(dscale(vp, sn), dscale(ev, c));
-      }
-      __syncthreads();
-    }
-  }
-  // descending order, ties keep the lower index
-  if (tid == 0) {
-    for (int i = 0; i < W; ++i) perm[i] = i;
-    for (int i = 0; i < W; ++i) {
-      int best = i;
-      for (int j = i + 1; j < W; ++j) {
-        const double vj = A[perm[j] * WP + perm[j]].x, vb = A[perm[best] * WP + perm[best]].x;
-        if (vj > vb || (vj == vb && perm[j] < perm[best])) best = j;
-      }
-      int t = perm[i];
-      perm[i] = perm[best];
-      perm[best] = t;
-    }
-  }
-  __syncthreads();
-  if (tid < W) evals[jj * W + tid] = A[perm[tid] * WP + perm[tid]].x;
-  dc* dst = reinterpret_cast<dc*>(evecs) + jj * W * W;
-  for (int i = tid; i < W * W; i += JT) {
-    const int r = i / W, c = i % W;
-    dst[i] = V[r * WP + perm[c]];
-  }
-}
 
 // ------------------------------------------------------------------ PCA projection coefficients
 // Pair i = component c1 + i: rows 2i (Re Y), 2i+1 (Im Y); columns 2t + comp:
@@ -1021,27 +847,6 @@ hv_status launch_gram_reduce(const float* part, int nwin, int nblk, int window, 
   dim3 grid((window * window + 255) / 256, nwin);
   hipLaunchKernelGGL(k_gram_reduce, grid, dim3(256), 0, st, part, nblk, window, cscale, cov);
   return launched("gram_reduce");
-}
-
-hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, double* evecs, double* offdiag,
-                        int max_sweeps, hipStream_t st) {
-  if (nwin <= 0) return HV_OK;
-  switch (window) {
-    case 16:
-      hipLaunchKernelGGL(k_jacobi<16>, dim3(nwin), dim3(jacobi_threads<16>()), 0, st, cov, evals, evecs, offdiag,
-                         max_sweeps);
-      break;
-    case 32:
-      hipLaunchKernelGGL(k_jacobi<32>, dim3(nwin), dim3(jacobi_threads<32>()), 0, st, cov, evals, evecs, offdiag,
-                         max_sweeps);
-      break;
-    case 64:
-      hipLaunchKernelGGL(k_jacobi<64>, dim3(nwin), dim3(jacobi_threads<64>()), 0, st, cov, evals, evecs, offdiag,
-                         max_sweeps);
-      break;
-    default: return fail(HV_ERR_SHAPE, "PCA window %d not supported", window);
-  }
-  return launched("jacobi");
 }
 
 hv_status launch_proj_coefs(const double* evecs, int nwin, int window, int c1, int c2, int mtiles, float* a32,
