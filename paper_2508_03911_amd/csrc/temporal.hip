@@ -371,6 +371,14 @@ __global__ __launch_bounds__(NT) void k_time_fft(const TIN* __restrict__ u, int 
 // MFMAs, so the loads are in flight while the matrix cores work.  Pixel
 // ranges are multiples of GP and frames a multiple of 4 pixels, so a run
 // lies wholly inside or wholly outside the range.
+//
+// G is symmetric, so only the 32 x 32 tiles on and above the diagonal are
+// formed, one per wave (10 of 16 at W = 64, 3 of 4 at W = 32); each sum keeps
+// its order, and a mirrored entry would hold the same bits.  FP32, bound by the
+// matrix cores: 8 windows of 64 frames of 512^2 656 -> 441 us (43 GFLOP of
+// tiles at 97 TFLOP/s), 32 windows of 32 frames of 384^2 482 -> 382 us (3.2 TB/s
+// of field reads); fp16, bound by the field reads: 280 us for four windows of
+// 1024^2 (3.8 TB/s), as before.
 constexpr int GP = 64;  // pixels per LDS tile
 
 template <typename TIN> struct Run4;
@@ -415,13 +423,17 @@ template <> struct Run4<float2> {  // 4 float pairs
   }
 };
 
+template <int W>
+constexpr int gram_tiles() {
+  return (2 * W / 32) * (2 * W / 32 + 1) / 2;
+}
+
 template <int W, bool MIXED, typename TIN>
-__global__ __launch_bounds__(NT) void k_gram(const TIN* __restrict__ u, long npix, int stride, long pix_per_blk,
+__global__ __launch_bounds__((64 * gram_tiles<W>())) void k_gram(const TIN* __restrict__ u, long npix, int stride, long pix_per_blk,
                                              float bsc, float* __restrict__ part, int nblk) {
   constexpr int M = 2 * W;
   constexpr int T = M / 32;             // tiles per dimension
-  constexpr int NW = NT / 64;
-  constexpr int TPW = (T * T + NW - 1) / NW;  // tiles per wave
+  constexpr int NT = 64 * gram_tiles<W>();
   constexpr int LS32 = GP + 1;          // f32 row stride (odd)
   constexpr int LS16 = GP + 8;          // fp16 row stride (keeps 16-byte reads aligned)
   constexpr int RUNS = W * GP / 4;      // 4-pixel runs per tile
@@ -435,11 +447,15 @@ __global__ __launch_bounds__(NT) void k_gram(const TIN* __restrict__ u, long npi
   const int blk = blockIdx.x;
   const long pbeg = (long)blk * pix_per_blk;
   const long pend = pbeg + pix_per_blk < npix ? pbeg + pix_per_blk : npix;
-  f32x16 acc[TPW];
+  // tile (mt, nt), mt <= nt, of this wave
+  int mt = 0, nt = wave;
+  while (nt >= T) {
+    ++mt;
+    nt -= T - mt;
+  }
+  f32x16 acc;
 #pragma unroll
-  for (int i = 0; i < TPW; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   const TIN* src = u + (jj * stride) * npix;
   // run q = tid + i * NT of a tile: frame q / (GP / 4), pixels 4 (q % (GP / 4)) + 0..3
   Run4<TIN> nxt[PER];
@@ -484,53 +500,39 @@ __global__ __launch_bounds__(NT) void k_gram(const TIN* __restrict__ u, long npi
     }
     __syncthreads();
     if (p0 + GP < pend) fetch(p0 + GP);
+    const int ma = 32 * mt + (lane & 31), nb = 32 * nt + (lane & 31);
     if constexpr (MIXED) {
 #pragma unroll
-      for (int i = 0; i < TPW; ++i) {
-        const int tile = wave + NW * i;
-        if (tile < T * T) {
-          const int mt = tile / T, nt = tile % T;
-          const int ma = 32 * mt + (lane & 31), nb = 32 * nt + (lane & 31);
-#pragma unroll
-          for (int kk = 0; kk < GP / 16; ++kk) {
-            hv_h8 a = *reinterpret_cast<const hv_h8*>(&l16[ma * LS16 + 16 * kk + 8 * h]);
-            hv_h8 b = *reinterpret_cast<const hv_h8*>(&l16[nb * LS16 + 16 * kk + 8 * h]);
-            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc[i], 0, 0, 0);
-          }
-        }
+      for (int kk = 0; kk < GP / 16; ++kk) {
+        hv_h8 a = *reinterpret_cast<const hv_h8*>(&l16[ma * LS16 + 16 * kk + 8 * h]);
+        hv_h8 b = *reinterpret_cast<const hv_h8*>(&l16[nb * LS16 + 16 * kk + 8 * h]);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc, 0, 0, 0);
       }
     } else {
-      // the wave's tiles interleaved per k-step (independent accumulators),
-      // each step's operands read from LDS one step ahead of its MFMAs; each
-      // accumulator sees its k-steps in the same order as one tile at a time
-      const float* ap[TPW];
-      const float* bp[TPW];
+      // each batch of k-steps' operands is read from LDS ahead of the MFMAs of
+      // the one before
+      constexpr int KB = 4;
+      const float* ap = l32 + ma * LS32 + h;
+      const float* bp = l32 + nb * LS32 + h;
+      float a[KB], b[KB];
 #pragma unroll
-      for (int i = 0; i < TPW; ++i) {
-        const int tile = min(wave + NW * i, T * T - 1), mt = tile / T, nt = tile % T;
-        ap[i] = l32 + (32 * mt + (lane & 31)) * LS32 + h;
-        bp[i] = l32 + (32 * nt + (lane & 31)) * LS32 + h;
-      }
-      float a[TPW], b[TPW];
-#pragma unroll
-      for (int i = 0; i < TPW; ++i) {
-        a[i] = ap[i][0];
-        b[i] = bp[i][0];
+      for (int i = 0; i < KB; ++i) {
+        a[i] = ap[2 * i];
+        b[i] = bp[2 * i];
       }
 #pragma unroll
-      for (int kk = 0; kk < GP / 2; ++kk) {
-        float an[TPW], bn[TPW];
+      for (int k0 = 0; k0 < GP / 2; k0 += KB) {
+        float an[KB], bn[KB];
 #pragma unroll
-        for (int i = 0; i < TPW; ++i) {
-          an[i] = kk + 1 < GP / 2 ? ap[i][2 * (kk + 1)] : 0.f;
-          bn[i] = kk + 1 < GP / 2 ? bp[i][2 * (kk + 1)] : 0.f;
+        for (int i = 0; i < KB; ++i) {
+          an[i] = k0 + KB < GP / 2 ? ap[2 * (k0 + KB + i)] : 0.f;
+          bn[i] = k0 + KB < GP / 2 ? bp[2 * (k0 + KB + i)] : 0.f;
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < TPW; ++i)
-          if (wave + NW * i < T * T) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc[i], 0, 0, 0);
+        for (int i = 0; i < KB; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < TPW; ++i) {
+        for (int i = 0; i < KB; ++i) {
           a[i] = an[i];
           b[i] = bn[i];
         }
@@ -539,37 +541,53 @@ __global__ __launch_bounds__(NT) void k_gram(const TIN* __restrict__ u, long npi
   }
   float* dst = part + (jj * nblk + blk) * (long)M * M;
 #pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    const int tile = wave + NW * i;
-    if (tile < T * T) {
-      const int mt = tile / T, nt = tile % T;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = 32 * mt + 8 * (r / 4) + 4 * h + (r % 4);
-        const int n = 32 * nt + (lane & 31);
-        dst[m * M + n] = acc[i][r];
-      }
-    }
+  for (int r = 0; r < 16; ++r) {
+    const int m = 32 * mt + 8 * (r / 4) + 4 * h + (r % 4);
+    const int n = 32 * nt + (lane & 31);
+    dst[m * M + n] = acc[r];
   }
 }
 
-// C[a][b] = sum_blk G[2a][2b] + G[2a+1][2b+1] + i (G[2a][2b+1] - G[2a+1][2b]),
-// summed in f64 in block order (deterministic).
-__global__ void k_gram_reduce(const float* __restrict__ part, int nblk, int W, double cscale,
-                              double* __restrict__ cov) {
+// C[a][b] = sum_blk G[2a][2b] + G[2a+1][2b+1] + i (G[2a][2b+1] - G[2a+1][2b])
+// for a <= b (the tiles that k_gram writes) and its conjugate at (b, a), summed
+// in f64 in a fixed order: RSEG threads take every RSEG-th block each, so that
+// the reads of a sum are not one chain (118 us for 256 blocks of four W = 64
+// windows with one thread an entry).
+constexpr int RSEG = 8;
+__global__ __launch_bounds__(32 * RSEG) void k_gram_reduce(const float* __restrict__ part, int nblk, int W,
+                                                           double cscale, double* __restrict__ cov) {
+  __shared__ double sre[RSEG][32], sim[RSEG][32];
   const long jj = blockIdx.y;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= W * W) return;
+  const int e = threadIdx.x & 31, seg = threadIdx.x >> 5;
+  const int idx = blockIdx.x * 32 + e;  // W * W is a multiple of 32
   const int a = idx / W, b = idx % W;
   const int M = 2 * W;
   double re = 0.0, im = 0.0;
-  for (int blk = 0; blk < nblk; ++blk) {
-    const float* g = part + (jj * nblk + blk) * (long)M * M;
-    re += (double)g[(2 * a) * M + 2 * b] + (double)g[(2 * a + 1) * M + 2 * b + 1];
-    im += (double)g[(2 * a) * M + 2 * b + 1] - (double)g[(2 * a + 1) * M + 2 * b];
+  if (a <= b) {
+    const float* g = part + jj * nblk * (long)M * M + (2 * a) * M + 2 * b;
+#pragma unroll 4
+    for (int blk = seg; blk < nblk; blk += RSEG) {
+      const float2 r0 = *reinterpret_cast<const float2*>(g + blk * (long)M * M);
+      const float2 r1 = *reinterpret_cast<const float2*>(g + blk * (long)M * M + M);
+      re += (double)r0.x + (double)r1.y;
+      im += (double)r0.y - (double)r1.x;
+    }
   }
-  cov[(jj * W * W + idx) * 2] = re * cscale;
-  cov[(jj * W * W + idx) * 2 + 1] = im * cscale;
+  sre[seg][e] = re;
+  sim[seg][e] = im;
+  __syncthreads();
+  if (seg != 0 || a > b) return;
+  for (int s = 1; s < RSEG; ++s) {
+    re += sre[s][e];
+    im += sim[s][e];
+  }
+  double* c = cov + jj * W * W * 2;
+  c[(a * W + b) * 2] = re * cscale;
+  c[(a * W + b) * 2 + 1] = im * cscale;
+  if (a < b) {
+    c[(b * W + a) * 2] = re * cscale;
+    c[(b * W + a) * 2 + 1] = -im * cscale;
+  }
 }
 
 // ------------------------------------------------------------------ FP64 complex values
@@ -759,12 +777,13 @@ void go_field(const void* u, bool half_in, long npix, int stride, int nwin, cons
 template <int W, bool MIXED>
 void go_gram(const void* u, bool half_in, long npix, int stride, int nwin, long ppb, float bsc, float* part,
              int nblk, hipStream_t st) {
+  constexpr int THREADS = 64 * gram_tiles<W>();
   dim3 grid(nblk, nwin);
   if (half_in)
-    hipLaunchKernelGGL((k_gram<W, MIXED, hv_h2>), grid, dim3(NT), 0, st, (const hv_h2*)u, npix, stride, ppb, bsc,
+    hipLaunchKernelGGL((k_gram<W, MIXED, hv_h2>), grid, dim3(THREADS), 0, st, (const hv_h2*)u, npix, stride, ppb, bsc,
                        part, nblk);
   else
-    hipLaunchKernelGGL((k_gram<W, MIXED, float2>), grid, dim3(NT), 0, st, (const float2*)u, npix, stride, ppb,
+    hipLaunchKernelGGL((k_gram<W, MIXED, float2>), grid, dim3(THREADS), 0, st, (const float2*)u, npix, stride, ppb,
                        bsc, part, nblk);
 }
 
@@ -844,8 +863,8 @@ hv_status launch_gram_partials(const void* u, bool half_in, long npix, int strid
 hv_status launch_gram_reduce(const float* part, int nwin, int nblk, int window, double cscale, double* cov,
                              hipStream_t st) {
   if (nwin <= 0) return HV_OK;
-  dim3 grid((window * window + 255) / 256, nwin);
-  hipLaunchKernelGGL(k_gram_reduce, grid, dim3(256), 0, st, part, nblk, window, cscale, cov);
+  dim3 grid(window * window / 32, nwin);  // windows are 16, 32 or 64
+  hipLaunchKernelGGL(k_gram_reduce, grid, dim3(32 * RSEG), 0, st, part, nblk, window, cscale, cov);
   return launched("gram_reduce");
 }
 
