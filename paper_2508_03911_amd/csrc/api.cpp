@@ -244,7 +244,19 @@ static hv_status build_dft_plan(size_t* held, DftPlan& p) {
         rhi[((size_t)m_t * ks + kk) * 64 + lane] = h;
         rlo[((size_t)m_t * ks + kk) * 64 + lane] = l;
       }
-  hv_status st = p.a32.upload(a32.data(), a32.size() * sizeof(float), held);
+  std::vector<float> wk((size_t)2 * w, 0.f);
+  std::vector<int> index((size_t)w, 0);
+  p.mask = 0;
+  for (int b = 0; b < nb; ++b) {
+    const int k = p.bins[b];
+    p.mask |= (uint64_t)1 << k;
+    index[k] = b;
+    wk[k] = wts[mt * 16 + b];
+    wk[w + k] = wts[2 * mt * 16 + b];
+  }
+  hv_status st = p.wk.upload(wk.data(), wk.size() * sizeof(float), held);
+  if (!st) st = p.index.upload(index.data(), index.size() * sizeof(int), held);
+  if (!st) st = p.a32.upload(a32.data(), a32.size() * sizeof(float), held);
   if (!st) st = p.ar_hi.upload(rhi.data(), rhi.size() * sizeof(hv_h8), held);
   if (!st) st = p.ar_lo.upload(rlo.data(), rlo.size() * sizeof(hv_h8), held);
   if (!st) st = p.a16hi.upload(hi.data(), hi.size() * sizeof(hv_h8), held);
@@ -886,7 +898,7 @@ static hv_status stft_band_first(Ctx* ctx, const void* in, int in_t, int ny, int
 // call (frames from j0 * stride), spatial passes then the temporal GEMM with
 // the moment epilogue; outputs at window j0 of m0/m1/m2/spec.
 static hv_status frames_first_chunk(Ctx* ctx, const void* in, int in_t, int ny, int nx, const hv_optics& o,
-                                    const CoefGemm& g, int nb, int w, int stride, int j0, int g_n, bool mixed,
+                                    const CoefGemm& g, const FieldBand& band, int nb, int w, int stride, int j0, int g_n, bool mixed,
                                     float* m0, float* m1, float* m2, float2* spec, hipStream_t st,
                                     const FixedWs* fixed) {
   hv_status s;
@@ -910,8 +922,8 @@ static hv_status frames_first_chunk(Ctx* ctx, const void* in, int in_t, int ny, 
     });
   }
   return run(ctx, "field_coef", st, fixed, [&] {
-    return launch_field_coef(so.f, so.half, (long)frame, stride, g_n, g, mixed, 1.f, 1.f / so.f_scale, o0, o1, o2,
-                             os, st);
+    return launch_field_dft(so.f, so.half, (long)frame, stride, g_n, band, nullptr, 0, w - 1, 1.f / so.f_scale, o0,
+                            o1, o2, os, st);
   });
 }
 
@@ -960,9 +972,8 @@ static hv_status stft_impl(hv_ctx* ctx, const void* in, int in_t, int n, int ny,
              (const hv_h8*)dp->a16lo.ptr, (const float*)dp->wts.ptr, 3};
   const int nb = (int)dp->bins.size();
   if (!optics) {
-    const float bsc = mixed ? fp16_field_scale(HV_C64, ny, nx) : 1.f;
-    return launch_field_coef(in, false, (long)frame, stride, nwin_total, g, mixed, bsc, mixed ? 1.f / bsc : 1.f, m0,
-                             m1, m2, spec, st);
+    return launch_field_dft(in, false, (long)frame, stride, nwin_total, dp->band(), nullptr, 0, w - 1, 1.f, m0, m1,
+                            m2, spec, st);
   }
   if (optics->method == HV_AS && band_first_fits(ny, nx, in_t) && ctx->stft_order != HV_ORDER_FRAMES_FIRST &&
       (ctx->stft_order == HV_ORDER_BAND_FIRST || band_first_cheaper(w, stride, nb, (int)in_elem(in_t), mixed))) {
@@ -991,7 +1002,7 @@ static hv_status stft_impl(hv_ctx* ctx, const void* in, int in_t, int n, int ny,
   for (int j0 = 0, c = 0; j0 < nwin_total && res == HV_OK; j0 += gw, ++c) {
     st = (l2 && (c & 1)) ? l2->s : caller;
     const int g_n = nwin_total - j0 < gw ? nwin_total - j0 : gw;
-    res = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, g, nb, w, stride, j0, g_n, mixed, m0, m1, m2, spec, st,
+    res = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, g, dp->band(), nb, w, stride, j0, g_n, mixed, m0, m1, m2, spec, st,
                              nullptr);
   }
   if (l2) {  // join, also after an error, so no work of this call outlives it on the second stream
@@ -1041,9 +1052,8 @@ hv_status hv_stft_moments_noalloc(hv_ctx* ctx, const void* in, int in_t, int n, 
              (const hv_h8*)dp->a16lo.ptr, (const float*)dp->wts.ptr, 3};
   const int nb = (int)dp->bins.size();
   if (!optics) {  // a field in memory: the temporal kernel alone, no workspace
-    const float bsc = mixed ? fp16_field_scale(HV_C64, ny, nx) : 1.f;
-    return launch_field_coef(in, false, (long)frame, stride, nwin_total, g, mixed, bsc, mixed ? 1.f / bsc : 1.f, m0,
-                             m1, m2, nullptr, st);
+    return launch_field_dft(in, false, (long)frame, stride, nwin_total, dp->band(), nullptr, 0, w - 1, 1.f, m0, m1,
+                            m2, nullptr, st);
   }
   void* base = nullptr;
   if ((s = scratch_of(ctx->device, &base))) return s;
@@ -1077,7 +1087,7 @@ hv_status hv_stft_moments_noalloc(hv_ctx* ctx, const void* in, int in_t, int n, 
   }
   for (int j0 = 0; j0 < nwin_total; j0 += gw) {
     const int g_n = nwin_total - j0 < gw ? nwin_total - j0 : gw;
-    if ((s = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, g, nb, w, stride, j0, g_n, mixed, m0, m1, m2,
+    if ((s = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, g, dp->band(), nb, w, stride, j0, g_n, mixed, m0, m1, m2,
                                 nullptr, st, &fx)))
       return s;
   }
@@ -1258,17 +1268,23 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
   if (gw < 1) gw = 1;
   // per-window scratch of one chunk, one set per stream
   struct Scratch {
-    void *part, *cv, *ev, *vec, *a32, *a16h, *a16l, *log;
+    void *part, *cv, *ev, *vec, *a32, *a16h, *a16l, *log, *vec32;
   };
   const size_t M = 2 * (size_t)w;
+  // Few components left out (or, PCA, few kept): one lane per pixel takes them
+  // out of its samples (or sums them); else the coefficient GEMM over the
+  // components kept, with its per-window coefficients.
+  const bool half_field = mixed && optics;
+  const bool direct = ssa ? field_dft_fits(half_field, w, comp_lo, comp_hi)
+                          : field_energy_fits(half_field, w, comp_lo, comp_hi);
   auto scratch = [&](hipStream_t cs, Scratch* x) -> hv_status {
-    const size_t bytes[8] = {(size_t)gw * nblk * M * M * 4, (size_t)gw * w * w * 16, (size_t)gw * w * 8,
-                             (size_t)gw * w * w * 16, (size_t)gw * mtiles * w * 64 * 4,
-                             (size_t)gw * mtiles * (w / 8) * 64 * 16, (size_t)gw * mtiles * (w / 8) * 64 * 16,
-                             jacobi_log_bytes(gw, w, kJacobiSweeps)};
-    void** dst[8] = {&x->part, &x->cv, &x->ev, &x->vec, &x->a32, &x->a16h, &x->a16l, &x->log};
-    const int slot[8] = {10, 11, 12, 13, 14, 15, 16, 18};
-    for (int i = 0; i < 8; ++i) {
+    const size_t coefs = direct ? 0 : (size_t)gw * mtiles * w * 64;
+    const size_t bytes[9] = {(size_t)gw * nblk * M * M * 4, (size_t)gw * w * w * 16, (size_t)gw * w * 8,
+                             (size_t)gw * w * w * 16, coefs * 4, coefs * 2, coefs * 2,
+                             jacobi_log_bytes(gw, w, kJacobiSweeps), (size_t)gw * w * w * 8};
+    void** dst[9] = {&x->part, &x->cv, &x->ev, &x->vec, &x->a32, &x->a16h, &x->a16l, &x->log, &x->vec32};
+    const int slot[9] = {10, 11, 12, 13, 14, 15, 16, 18, 19};
+    for (int i = 0; i < 9; ++i) {
       DevBuf& b = ctx->work(cs, slot[i]);
       hv_status e = b.ensure(bytes[i], &ctx->held);
       if (e) return e;
@@ -1279,7 +1295,7 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
   const float* wts = nullptr;
   if (ssa) {
     wts = (const float*)ssa->wts.ptr;  // f_k^n of the band bins, as the STFT path
-  } else {
+  } else if (!direct) {
     DevBuf& wb = ctx->work(st, 17);  // read-only, shared by both streams
     std::vector<float> hw((size_t)3 * mtiles * 16, 0.f);
     for (int i = 0; i < npair; ++i) hw[i] = 1.f;
@@ -1332,11 +1348,25 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
         return s;
       if ((s = timed(ctx, "jacobi", st, [&] {
              return launch_jacobi((const double*)x.cv, g_n, w, (double*)x.ev, (double*)x.vec,
-                                  o.offdiag ? o.offdiag + j0 : nullptr, kJacobiSweeps, x.log, st);
+                                  o.offdiag ? o.offdiag + j0 : nullptr, kJacobiSweeps, x.log,
+                                  (float2*)x.vec32, st);
            })))
         return s;
       const size_t at = (size_t)j0 * frame;
-      if (ssa) {
+      if (ssa && direct) {
+        if ((s = timed(ctx, "ssa_moments", st, [&] {
+               return launch_field_dft(field, half, (long)frame, stride, g_n, ssa->band(), (const float2*)x.vec32,
+                                       comp_lo, comp_hi, half ? 1.f / fs : 1.f, o.m0 ? o.m0 + at : nullptr,
+                                       o.m1 ? o.m1 + at : nullptr, o.m2 ? o.m2 + at : nullptr, nullptr, st);
+             })))
+          return s;
+      } else if (direct) {
+        if ((s = timed(ctx, "proj_energy", st, [&] {
+               return launch_field_energy(field, half, (long)frame, stride, g_n, w, (const float2*)x.vec32, comp_lo,
+                                          comp_hi, half ? 1.f / fs : 1.f, o.m0 + at, st);
+             })))
+          return s;
+      } else if (ssa) {
         if ((s = launch_ssa_coefs((const double*)x.vec, g_n, w, comp_lo, comp_hi, ssa->bins.data(), npair, mtiles,
                                   (float*)x.a32, (hv_h8*)x.a16h, (hv_h8*)x.a16l, st)))
           return s;

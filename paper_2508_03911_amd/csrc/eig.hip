@@ -296,7 +296,8 @@ constexpr int WAVE_SHL1 = 0x130, WAVE_SHR1 = 0x138;
 // only chain is a row's own rotations, with the next steps' parameters loaded
 // ahead.
 template <int W>
-__global__ __launch_bounds__(128) void k_jacobi_vectors(JacobiLog log, double* __restrict__ evecs) {
+__global__ __launch_bounds__(128) void k_jacobi_vectors(JacobiLog log, double* __restrict__ evecs,
+                                                        float2* __restrict__ vec32) {
   constexpr int H = W / 2, AHEAD = W >= 32 ? 16 : 8;  // steps in flight: the log comes from another XCD
   const long jj = blockIdx.y;
   const int q = blockIdx.x * 128 + threadIdx.x;
@@ -350,13 +351,16 @@ __global__ __launch_bounds__(128) void k_jacobi_vectors(JacobiLog log, double* _
   dc* dst = reinterpret_cast<dc*>(evecs) + (jj * W + row) * W;
   dst[rank[k]] = t;
   dst[rank[W - 1 - k]] = b;
+  float2* v = vec32 + jj * W * W + row;
+  v[rank[k] * W] = make_float2((float)t.x, (float)t.y);
+  v[rank[W - 1 - k] * W] = make_float2((float)b.x, (float)b.y);
 }
 
 template <int W>
 void go_jacobi(const double* cov, int nwin, double* evals, double* evecs, double* offdiag, const JacobiLog& log,
-               hipStream_t st) {
+               float2* vec32, hipStream_t st) {
   hipLaunchKernelGGL(k_jacobi<W>, dim3(nwin), dim3(JacobiShape<W>::NA), 0, st, cov, evals, offdiag, log);
-  hipLaunchKernelGGL(k_jacobi_vectors<W>, dim3(W * W / 2 / 128, nwin), dim3(128), 0, st, log, evecs);
+  hipLaunchKernelGGL(k_jacobi_vectors<W>, dim3(W * W / 2 / 128, nwin), dim3(128), 0, st, log, evecs, vec32);
 }
 
 }  // namespace
@@ -372,7 +376,7 @@ size_t jacobi_log_bytes(int nwin, int window, int max_sweeps) {
 }
 
 hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, double* evecs, double* offdiag,
-                        int max_sweeps, void* log_ws, hipStream_t st) {
+                        int max_sweeps, void* log_ws, float2* vec32, hipStream_t st) {
   if (nwin <= 0) return HV_OK;
   const size_t n = log_entries(nwin, window, max_sweeps);
   JacobiLog log;
@@ -382,9 +386,9 @@ hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, 
   log.rank = log.steps + nwin;
   log.max_sweeps = max_sweeps;
   switch (window) {
-    case 16: go_jacobi<16>(cov, nwin, evals, evecs, offdiag, log, st); break;
-    case 32: go_jacobi<32>(cov, nwin, evals, evecs, offdiag, log, st); break;
-    case 64: go_jacobi<64>(cov, nwin, evals, evecs, offdiag, log, st); break;
+    case 16: go_jacobi<16>(cov, nwin, evals, evecs, offdiag, log, vec32, st); break;
+    case 32: go_jacobi<32>(cov, nwin, evals, evecs, offdiag, log, vec32, st); break;
+    case 64: go_jacobi<64>(cov, nwin, evals, evecs, offdiag, log, vec32, st); break;
     default: return fail(HV_ERR_SHAPE, "PCA window %d not supported", window);
   }
   const hipError_t e = hipGetLastError();

@@ -76,10 +76,29 @@ hv_status launch_rowinv_coef(const void* z, bool half_in, int ny, int nx, int st
                              const CoefGemm& g, bool mixed, float b_scale, float out_scale, float* out0,
                              float* out1, float* out2, float2* spec, hipStream_t st);
 
-// Unfused: field chunk [nf][P] (P = ny*nx) already in memory.
-hv_status launch_field_coef(const void* u, bool half_in, long npix, int stride, int nwin,
-                            const CoefGemm& g, bool mixed, float b_scale, float out_scale, float* out0,
-                            float* out1, float* out2, float2* spec, hipStream_t st);
+// The band of a DFT plan for the kernels that transform a pixel's samples in
+// registers.
+struct FieldBand {
+  int window;        // W (8, 16, 32 or 64)
+  int npair;         // bins of the band
+  uint64_t mask;     // bit k: bin k belongs to it
+  const float* wk;   // [2][W]: f_k and f_k^2 (0 outside the band)
+  const int* index;  // [W]: place of bin k in the band
+};
+
+// Field chunk [nf][P] (P = ny*nx) in memory, one lane per pixel: moments and
+// band bins (spec, nullable) of the window, amplitudes * amp.  With vec
+// ([nwin][component][W], eigenvectors) the window is filtered onto components
+// c1..c2 first (SSA); field_dft_fits says whether few enough are left out.
+bool field_dft_fits(bool half_in, int window, int c1, int c2);
+hv_status launch_field_dft(const void* u, bool half_in, long npix, int stride, int nwin, const FieldBand& b,
+                           const float2* vec, int c1, int c2, float amp, float* out0, float* out1, float* out2,
+                           float2* spec, hipStream_t st);
+// Energy of components c1..c2 of every pixel, m0 [nwin][npix] (PCA), where few
+// components are kept or left out.
+bool field_energy_fits(bool half_in, int window, int c1, int c2);
+hv_status launch_field_energy(const void* u, bool half_in, long npix, int stride, int nwin, int window,
+                              const float2* vec, int c1, int c2, float amp, float* m0, hipStream_t st);
 
 bool rowinv_coef_fits(int nx, int window);
 
@@ -97,10 +116,11 @@ hv_status launch_gram_reduce(const float* part, int nwin, int nblk, int window, 
 // eigenvectors (columns, complex f64 interleaved) [nwin][W][W]; offdiag
 // (nullable) [nwin] receives sqrt(off-diagonal / total squared magnitude)
 // when the window stops (converged below 1e-15, or max_sweeps reached); log_ws:
-// 16-byte aligned workspace of jacobi_log_bytes for the rotations.
+// 16-byte aligned workspace of jacobi_log_bytes for the rotations; vec32
+// [nwin][component][W] receives the eigenvectors in single precision.
 size_t jacobi_log_bytes(int nwin, int window, int max_sweeps);
 hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, double* evecs, double* offdiag,
-                        int max_sweeps, void* log_ws, hipStream_t st);
+                        int max_sweeps, void* log_ws, float2* vec32, hipStream_t st);
 // Build per-window projection coefficient fragments from eigenvectors
 // columns c1..c2 (A = [Vr^T Vi^T ; ...]) for the coefficient GEMM.
 hv_status launch_proj_coefs(const double* evecs, int nwin, int window, int c1, int c2, int mtiles,

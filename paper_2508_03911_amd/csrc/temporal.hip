@@ -269,23 +269,11 @@ __global__ __launch_bounds__(NT) void k_rowinv_coef(const TIN* __restrict__ z, i
 // ------------------------------------------------------------------ GEMM from a field in memory
 constexpr int TPIX = NT / 2;  // pixel counts must be a multiple of this
 
-// Threads per block: one 32-pixel tile per wave, so a block covers
-// threads / 2 pixels.  A W = 64 tile of 256 pixels fills 140 KB of LDS and
-// leaves one block per CU, its loads and its MFMAs in turn.  DIV = 2 halves it
-// (128 pixels, four waves, 67 KB) so that two blocks share a CU and one's
-// loads run under the other's MFMAs.  Measured on 1024^2 fields: the STFT
-// GEMM 0.50 -> 0.445 ms per window with it; the PCA projection ran faster
-// too, but its pass slower (it shares the chip with the other stream's
-// eigensolve and covariance), so that one keeps the full tile.
-template <int W, int DIV>
-constexpr int coef_threads() {
-  return W >= 64 ? NT / DIV : NT;
-}
-
-template <int W, bool MIXED, typename TIN, int DIV>
-__global__ __launch_bounds__((coef_threads<W, DIV>())) void k_field_coef(const TIN* __restrict__ u, long npix,
-                                                                        int stride, CoefArgs g) {
-  constexpr int NTB = coef_threads<W, DIV>(), TP = NTB / 2;
+// One 32-pixel tile per wave; a W = 64 tile of 256 pixels fills 140 KB of LDS
+// and leaves one block per CU, its loads and its MFMAs in turn.
+template <int W, bool MIXED, typename TIN>
+__global__ __launch_bounds__(NT) void k_field_coef(const TIN* __restrict__ u, long npix, int stride, CoefArgs g) {
+  constexpr int NTB = NT, TP = TPIX;
   constexpr int S = lds_stride(TP);
   constexpr bool EXACT = MIXED && sizeof(TIN) == 4;  // fp16 storage is exact in fp16
   __shared__ float2 buf[W * S];
@@ -762,16 +750,13 @@ hv_status go_rowinv_w(const void* z, bool half_in, int ny, int nx, int stride, i
   return hvi::fail(HV_ERR_SHAPE, "nx=%d not supported", nx);
 }
 
-template <int W, bool MIXED, int DIV = 1>
+template <int W, bool MIXED>
 void go_field(const void* u, bool half_in, long npix, int stride, int nwin, const CoefArgs& a, hipStream_t st) {
-  constexpr int NTB = coef_threads<W, DIV>();
-  dim3 grid((unsigned)(npix / (NTB / 2)), nwin);
+  dim3 grid((unsigned)(npix / TPIX), nwin);
   if (half_in)
-    hipLaunchKernelGGL((k_field_coef<W, MIXED, hv_h2, DIV>), grid, dim3(NTB), 0, st, (const hv_h2*)u, npix,
-                       stride, a);
+    hipLaunchKernelGGL((k_field_coef<W, MIXED, hv_h2>), grid, dim3(NT), 0, st, (const hv_h2*)u, npix, stride, a);
   else
-    hipLaunchKernelGGL((k_field_coef<W, MIXED, float2, DIV>), grid, dim3(NTB), 0, st, (const float2*)u, npix,
-                       stride, a);
+    hipLaunchKernelGGL((k_field_coef<W, MIXED, float2>), grid, dim3(NT), 0, st, (const float2*)u, npix, stride, a);
 }
 
 template <int W, bool MIXED>
@@ -809,37 +794,20 @@ hv_status launch_rowinv_coef(const void* z, bool half_in, int ny, int nx, int st
   return fail(HV_ERR_SHAPE, "window %d not supported", g.window);
 }
 
-// half_tile: W = 64 runs two 128-pixel blocks per CU (the STFT GEMM) rather
-// than one of 256 pixels (the PCA projection).
 static hv_status field_coef(const void* u, bool half_in, long npix, int stride, int nwin, const CoefArgs& a,
-                            int window, bool mixed, bool half_tile, hipStream_t st) {
+                            int window, bool mixed, hipStream_t st) {
   if (nwin <= 0) return HV_OK;
   if (npix % TPIX) return fail(HV_ERR_SHAPE, "pixel count %ld not a multiple of %d", npix, TPIX);
   switch (window) {
-    case 8: mixed ? go_field<8, true>(u, half_in, npix, stride, nwin, a, st)
-                  : go_field<8, false>(u, half_in, npix, stride, nwin, a, st); break;
     case 16: mixed ? go_field<16, true>(u, half_in, npix, stride, nwin, a, st)
                    : go_field<16, false>(u, half_in, npix, stride, nwin, a, st); break;
     case 32: mixed ? go_field<32, true>(u, half_in, npix, stride, nwin, a, st)
                    : go_field<32, false>(u, half_in, npix, stride, nwin, a, st); break;
-    case 64:
-      if (half_tile)
-        mixed ? go_field<64, true, 2>(u, half_in, npix, stride, nwin, a, st)
-              : go_field<64, false, 2>(u, half_in, npix, stride, nwin, a, st);
-      else
-        mixed ? go_field<64, true>(u, half_in, npix, stride, nwin, a, st)
-              : go_field<64, false>(u, half_in, npix, stride, nwin, a, st);
-      break;
+    case 64: mixed ? go_field<64, true>(u, half_in, npix, stride, nwin, a, st)
+                   : go_field<64, false>(u, half_in, npix, stride, nwin, a, st); break;
     default: return fail(HV_ERR_SHAPE, "window %d not supported", window);
   }
   return launched("field_coef");
-}
-
-hv_status launch_field_coef(const void* u, bool half_in, long npix, int stride, int nwin, const CoefGemm& g,
-                            bool mixed, float b_scale, float out_scale, float* out0, float* out1, float* out2,
-                            float2* spec, hipStream_t st) {
-  CoefArgs a = make_args(g, 0, b_scale, out_scale, out0, out1, out2, spec);
-  return field_coef(u, half_in, npix, stride, nwin, a, g.window, mixed, true, st);
 }
 
 hv_status launch_gram_partials(const void* u, bool half_in, long npix, int stride, int nwin, int window,
@@ -903,7 +871,7 @@ hv_status launch_coef_moments(const void* u, bool half_in, long npix, int stride
                               hipStream_t st) {
   CoefGemm g{window, mtiles, npair, a32, a16hi, a16lo, wts, 3};
   CoefArgs a = make_args(g, (long)mtiles * window * 64, b_scale, out_scale, m0, m1, m2, nullptr);
-  return field_coef(u, half_in, npix, stride, nwin, a, window, mixed, false, st);
+  return field_coef(u, half_in, npix, stride, nwin, a, window, mixed, st);
 }
 
 hv_status launch_proj_energy(const void* u, bool half_in, long npix, int stride, int nwin, int window, int mtiles,
@@ -912,7 +880,7 @@ hv_status launch_proj_energy(const void* u, bool half_in, long npix, int stride,
                              hipStream_t st) {
   CoefGemm g{window, mtiles, npair, a32, a16hi, a16lo, wts, 1};
   CoefArgs a = make_args(g, (long)mtiles * window * 64, b_scale, out_scale, m0, nullptr, nullptr, nullptr);
-  return field_coef(u, half_in, npix, stride, nwin, a, window, mixed, false, st);
+  return field_coef(u, half_in, npix, stride, nwin, a, window, mixed, st);
 }
 
 hv_status launch_time_fft(const void* u, bool half_in, long npix, int stride, int nwin, int window, float amp2,
