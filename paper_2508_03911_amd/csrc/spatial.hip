@@ -513,17 +513,26 @@ void go_col_as(const void* in, void* out, const float2* hs, int n, int nx, hipSt
                      (TIO*)out, hs, nx, n % 8 == 0);
 }
 
-template <int NX, typename TIN, typename TOUT>
+// Rows per tile of the general row passes: a height of 800 is no multiple of
+// the 64 rows that narrow frames take, but of 32.
+template <int NX>
+constexpr int row_tile() {
+  return cap64(p2floor(8192 / NX));
+}
+
+template <int NX, typename TIN, typename TOUT, int ROWS = row_tile<NX>()>
 void go_row_inv(const void* in, void* out, int n, int ny, float scale, hipStream_t st) {
-  constexpr int ROWS = cap64(p2floor(8192 / NX));
+  if constexpr (ROWS > 32)
+    if (ny % ROWS) return go_row_inv<NX, TIN, TOUT, 32>(in, out, n, ny, scale, st);
   hipLaunchKernelGGL((k_row_inv<NX, ROWS, TIN, TOUT>), dim3(ny / ROWS, n), dim3(NT), 0, st, (const TIN*)in,
                      (TOUT*)out, ny, scale);
 }
 
-template <int NX, typename TIN, typename TOUT>
+template <int NX, typename TIN, typename TOUT, int ROWS = row_tile<NX>()>
 void go_rows(const void* in, void* out, const float2* qx, const float2* qy, int dir, int n, int ny, float scale,
              hipStream_t st) {
-  constexpr int ROWS = cap64(p2floor(8192 / NX));
+  if constexpr (ROWS > 32)
+    if (ny % ROWS) return go_rows<NX, TIN, TOUT, 32>(in, out, qx, qy, dir, n, ny, scale, st);
   if (dir < 0)
     hipLaunchKernelGGL((k_rows_c2c<NX, ROWS, TIN, TOUT, -1>), dim3(ny / ROWS, n), dim3(NT), 0, st,
                        (const TIN*)in, (TOUT*)out, qx, qy, ny, scale);
