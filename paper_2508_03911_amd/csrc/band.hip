@@ -215,17 +215,17 @@ __global__ __launch_bounds__(NTK) void k_band_cols(TIO* __restrict__ io, const f
   for (; unit < nunits; unit += gridDim.x) {
     TIO* base = base_of(unit);
 #pragma unroll
-    for (int u = 0; u < U; ++u) buf[s * S + skew(yr + u * RS)] = load_c(&pre[u]);
+    for (int u = 0; u < U; ++u) buf[s * S + place<NY>(yr + u * RS)] = load_c(&pre[u]);
     __syncthreads();
     if (unit + (int)gridDim.x < nunits) fetch(unit + gridDim.x);
     fft_lds_io<NY, BC, NTK, -1, true>(buf, tw, tid, nullptr, [&](int u, int r, int b, int i, float2 v) {
-      buf[b * S + skew(i)] = c2::mul(v, hv[u][r]);
+      buf[b * S + place<NY>(i)] = c2::mul(v, hv[u][r]);
     });
     fft_lds<NY, BC, NTK, +1>(buf, tw, tid);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       TIO v;
-      store_c(&v, buf[s * S + skew(yr + u * RS)]);
+      store_c(&v, buf[s * S + place<NY>(yr + u * RS)]);
       st_off(base + (long)u * RS * nx, off, v);
     }
     __syncthreads();

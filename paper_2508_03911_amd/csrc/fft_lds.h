@@ -8,9 +8,9 @@
 // workgroup barrier, then all writes, then another barrier.
 //
 // Layout of sequence b in LDS (float2 units): base b*STRIDE, element i at
-// i + (i >> 4).  The skew of one slot every 16 elements and an odd row
-// stride keep the strided butterfly writes and the transposed reads of the
-// callers off the same LDS banks.
+// place<N>(i) = i + (i >> 4) for powers of two.  The skew of one slot every 16
+// elements and an odd row stride keep the strided butterfly writes and the
+// transposed reads of the callers off the same LDS banks.
 //
 // Direction: DIR = -1 computes sum_m a[m] exp(-2 pi i k m / N) (forward),
 // DIR = +1 the unnormalised inverse.
@@ -37,10 +37,19 @@ struct c2 {
   }
 };
 
-// Skewed LDS index within one sequence.
+// Skewed LDS index within one sequence of a power-of-two length.
 __device__ __host__ constexpr inline int skew(int i) { return i + (i >> 4); }
-// Row stride (float2 units) for sequences of length N: skewed length + 1 (odd).
-__device__ __host__ constexpr inline int lds_stride(int n) { return n + (n >> 4) + 1; }
+// The mixed-radix lengths (320, 384, 800, 1280) start with radix 3 or 5 passes,
+// whose odd strides spread over the banks by themselves, and their later
+// strides are no multiples of 16, so a skew would cost an add and a shift for
+// every access where a plain index folds into the instruction's offset.
+__device__ __host__ constexpr inline bool skewed(int n) { return (n & (n - 1)) == 0; }
+template <int N>
+__device__ __host__ constexpr inline int place(int i) {
+  return skewed(N) ? skew(i) : i;
+}
+// Row stride (float2 units) for sequences of length N: length in LDS + 1 (odd).
+__device__ __host__ constexpr inline int lds_stride(int n) { return n + (skewed(n) ? n >> 4 : 0) + 1; }
 
 // ---------------------------------------------------------------- small DFTs
 
@@ -73,7 +82,7 @@ __device__ inline float2 w16(int m, int dir) {
 
 // R-point DFT of v[0..R) in registers, natural order in and out.
 template <int R, int DIR>
-__device__ inline void dft_reg(float2* v) {
+__device__ __forceinline__ void dft_reg(float2* v) {
   if constexpr (R == 2) {
     dft2<DIR>(v[0], v[1]);
   } else if constexpr (R == 3) {
@@ -196,7 +205,7 @@ constexpr int tw_offset(int n, int pass) {
 constexpr int tw_size(int n) { return tw_offset(n, num_passes(n)); }
 
 template <int N>
-__device__ inline void fill_twiddles(float2* tw, int tid, int nthreads) {
+__device__ __forceinline__ void fill_twiddles(float2* tw, int tid, int nthreads) {
   constexpr int P = num_passes(N);
   for (int p = 1; p < P; ++p) {
     const int ns = ns_of_pass(N, p), r_ = radix_of_pass(N, p), off = tw_offset(N, p);
@@ -206,6 +215,20 @@ __device__ inline void fill_twiddles(float2* tw, int tid, int nthreads) {
       sincospif(-2.0f * (float)((k * r) % (ns * r_)) / (float)(ns * r_), &s, &c);
       tw[off + e] = make_float2(c, s);
     }
+  }
+}
+
+// Orders LDS accesses of the NT threads that transform a tile together.  One
+// wave's LDS operations complete in order, so a single wave needs no barrier,
+// only that the compiler keeps their order.
+template <int NT>
+__device__ inline void tile_sync() {
+  if constexpr (NT == 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
   }
 }
 
@@ -219,7 +242,7 @@ __device__ inline void fill_twiddles(float2* tw, int tid, int nthreads) {
 // reads and the writes is kept when both touch LDS, the barrier after the
 // writes when the writes touch LDS.
 template <int N, int R, int NS, int NB, int NT, int DIR, int TWOFF, bool ST_LDS, class LD, class ST>
-__device__ inline void stockham_pass_io(float2* buf, const float2* tw, int tid, const LD& ld, const ST& st) {
+__device__ __forceinline__ void stockham_pass_io(float2* buf, const float2* tw, int tid, const LD& ld, const ST& st) {
   constexpr int BF = NB * (N / R);             // butterflies in the pass
   constexpr int U = (BF + NT - 1) / NT;        // per thread
   constexpr int S = lds_stride(N);
@@ -235,7 +258,7 @@ __device__ inline void stockham_pass_io(float2* buf, const float2* tw, int tid, 
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if constexpr (LDS_IN)
-          v[u][r] = src[skew(j + r * (N / R))];
+          v[u][r] = src[place<N>(j + r * (N / R))];
         else
           v[u][r] = ld(u, r, b, j + r * (N / R));
       }
@@ -251,7 +274,7 @@ __device__ inline void stockham_pass_io(float2* buf, const float2* tw, int tid, 
       dft_reg<R, DIR>(v[u]);
     }
   }
-  if constexpr (LDS_IN && (LDS_OUT || ST_LDS)) __syncthreads();
+  if constexpr (LDS_IN && (LDS_OUT || ST_LDS)) tile_sync<NT>();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     int q = tid + u * NT;
@@ -263,22 +286,22 @@ __device__ inline void stockham_pass_io(float2* buf, const float2* tw, int tid, 
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if constexpr (LDS_OUT)
-          dst[skew(base + r * NS)] = v[u][r];
+          dst[place<N>(base + r * NS)] = v[u][r];
         else
           st(u, r, b, base + r * NS, v[u][r]);
       }
     }
   }
-  if constexpr (LDS_OUT || ST_LDS) __syncthreads();
+  if constexpr (LDS_OUT || ST_LDS) tile_sync<NT>();
 }
 
 template <int N, int R, int NS, int NB, int NT, int DIR, int TWOFF>
-__device__ inline void stockham_pass(float2* buf, const float2* tw, int tid) {
+__device__ __forceinline__ void stockham_pass(float2* buf, const float2* tw, int tid) {
   stockham_pass_io<N, R, NS, NB, NT, DIR, TWOFF, false>(buf, tw, tid, nullptr, nullptr);
 }
 
 template <int N, int PASS, int NS, int NB, int NT, int DIR>
-__device__ inline void fft_passes(float2* buf, const float2* tw, int tid) {
+__device__ __forceinline__ void fft_passes(float2* buf, const float2* tw, int tid) {
   if constexpr (PASS < num_passes(N)) {
     constexpr int R = radix_of_pass(N, PASS);
     stockham_pass<N, R, NS, NB, NT, DIR, tw_offset(N, PASS)>(buf, tw, tid);
@@ -287,7 +310,7 @@ __device__ inline void fft_passes(float2* buf, const float2* tw, int tid) {
 }
 
 template <int N, int PASS, int NS, int NB, int NT, int DIR, bool ST_LDS, class LD, class ST>
-__device__ inline void fft_passes_io(float2* buf, const float2* tw, int tid, const LD& ld, const ST& st) {
+__device__ __forceinline__ void fft_passes_io(float2* buf, const float2* tw, int tid, const LD& ld, const ST& st) {
   if constexpr (PASS < num_passes(N)) {
     constexpr int R = radix_of_pass(N, PASS);
     constexpr bool FIRST = PASS == 0, LAST = PASS + 1 == num_passes(N);
@@ -334,11 +357,11 @@ constexpr int fft_last_slots() {
   return (NB * (N / radix_of_pass(N, num_passes(N) - 1)) + NT - 1) / NT;
 }
 
-// NB in-place FFTs of length N held in LDS at buf[b * lds_stride(N) + skew(i)].
+// NB in-place FFTs of length N held in LDS at buf[b * lds_stride(N) + place<N>(i)].
 // Requires a barrier before (data written) -- provided by the caller -- and
 // leaves a barrier after.  tw (tw_size(N) entries) must hold fill_twiddles<N>.
 template <int N, int NB, int NT, int DIR>
-__device__ inline void fft_lds(float2* buf, const float2* tw, int tid) {
+__device__ __forceinline__ void fft_lds(float2* buf, const float2* tw, int tid) {
   fft_passes<N, 0, 1, NB, NT, DIR>(buf, tw, tid);
 }
 
@@ -348,8 +371,63 @@ __device__ inline void fft_lds(float2* buf, const float2* tw, int tid) {
 // still orders earlier LDS reads of buf); with a store hook that does not
 // write buf (ST_LDS false) the call ends without a barrier.
 template <int N, int NB, int NT, int DIR, bool ST_LDS = false, class LD, class ST>
-__device__ inline void fft_lds_io(float2* buf, const float2* tw, int tid, const LD& ld, const ST& st) {
+__device__ __forceinline__ void fft_lds_io(float2* buf, const float2* tw, int tid, const LD& ld, const ST& st) {
   fft_passes_io<N, 0, 1, NB, NT, DIR, ST_LDS>(buf, tw, tid, ld, st);
+}
+
+// NB sequences by NT threads with every sequence inside one wave: wave w
+// transforms sequences w * RW .. (w + 1) * RW - 1, RW = NB / (NT / 64), so the
+// passes need no barrier and the waves of a workgroup run apart.  Falls back to
+// the whole workgroup where the sequences do not split evenly over the waves.
+template <int NB, int NT>
+constexpr bool wave_tile() {
+  return NB % (NT / 64) == 0;
+}
+// Load slot i of this thread is element x of sequence b of the tile: a wave
+// loads its own sequences, so no barrier is needed between the loads and the
+// transform.  False past the end of the wave's (or the tile's) elements.
+template <int N, int NB, int NT>
+__device__ __forceinline__ bool tile_element(int tid, int i, int* b, int* x) {
+  if constexpr (wave_tile<NB, NT>()) {
+    constexpr int RW = NB / (NT / 64);
+    const int wave = tid >> 6, lane = tid & 63, e = lane + 64 * i;
+    if constexpr (N % 64 == 0) {  // a run of 64 stays inside one sequence
+      *b = wave * RW + 64 * i / N;
+      *x = lane + 64 * i % N;
+      return 64 * i < RW * N;
+    } else {
+      *b = wave * RW + (RW == 1 ? 0 : e / N);
+      *x = RW == 1 ? e : e % N;
+      return (RW * N) % 64 == 0 || e < RW * N;
+    }
+  } else {
+    const int q = tid + i * NT;
+    *b = q / N;
+    *x = q % N;
+    return (NB * N) % NT == 0 || q < NB * N;
+  }
+}
+template <int N, int NB, int NT>
+constexpr int tile_slots() {
+  return wave_tile<NB, NT>() ? (NB / (NT / 64) * N + 63) / 64 : (NB * N + NT - 1) / NT;
+}
+// The transform; the caller puts a barrier after it before other threads read
+// the result, and (the fallback only) finds one before it in tile_ready.
+template <int N, int NB, int NT>
+__device__ inline void tile_ready() {
+  if constexpr (wave_tile<NB, NT>())
+    tile_sync<64>();
+  else
+    __syncthreads();
+}
+template <int N, int NB, int NT, int DIR>
+__device__ __forceinline__ void fft_tile(float2* buf, const float2* tw, int tid) {
+  if constexpr (wave_tile<NB, NT>()) {
+    constexpr int RW = NB / (NT / 64);
+    fft_lds<N, RW, 64, DIR>(buf + (tid >> 6) * RW * lds_stride(N), tw, tid & 63);
+  } else {
+    fft_lds<N, NB, NT, DIR>(buf, tw, tid);
+  }
 }
 
 }  // namespace hvk

@@ -313,24 +313,38 @@ __global__ __launch_bounds__(NT) void k_col_as(const TIO* __restrict__ in, TIO* 
   }
 }
 
-// A tile of E elements from src (element q at src + q, sequence-major) into
-// the LDS rows buf[(q / N) * S + skew(q % N)].  The trip count is fixed at
-// compile time, so every load is issued before the first LDS write.
-template <int N, int E, typename TIN>
-__device__ inline void load_tile(float2* buf, const TIN* __restrict__ src, int tid) {
-  constexpr int S = lds_stride(N), PER = (E + NT - 1) / NT;
+// The general row and column passes (K3, K4, complex columns): each wave loads,
+// transforms and (K3) stores sequences of its own, so the passes of a transform
+// need no workgroup barrier, only the transposed stores do.  The mixed-radix
+// sides also had their transforms compiled as calls with flat addressing; they
+// are inlined now, with plain LDS indices (fft_lds.h).  2^26 pixels, us, before
+// and after: fp16 rows and columns 384^2 203 -> 176 and 203 -> 157, 1024^2 149 ->
+// 132 and 166 -> 146; FP32 384^2 208 -> 182 and 228 -> 205, 1024^2 177 -> 157 and
+// 235 -> 224; complex AS columns 320^2 456 -> 309, 800^2 560 -> 392; K3 fp16
+// 384^2 205 -> 135.
+//
+// NB sequences of length N from src (sequence-major) into LDS.  The slot count
+// is fixed at compile time, so every load is issued before the first LDS write;
+// each wave takes the sequences it will transform (fft_tile).
+template <int N, int NB, typename TIN>
+struct Tile {
+  static constexpr int S = lds_stride(N), PER = tile_slots<N, NB, NT>();
   TIN v[PER];
+  __device__ inline void load(const TIN* __restrict__ src, int tid) {
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int q = tid + i * NT;
-    if (E % NT == 0 || q < E) v[i] = src[q];
+    for (int i = 0; i < PER; ++i) {
+      int b, x;
+      if (tile_element<N, NB, NT>(tid, i, &b, &x)) v[i] = src[b * N + x];
+    }
   }
+  __device__ inline void put(float2* buf, int tid) const {
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int q = tid + i * NT;
-    if (E % NT == 0 || q < E) buf[(q / N) * S + skew(q % N)] = load_c(&v[i]);
+    for (int i = 0; i < PER; ++i) {
+      int b, x;
+      if (tile_element<N, NB, NT>(tid, i, &b, &x)) buf[b * S + place<N>(x)] = load_c(&v[i]);
+    }
   }
-}
+};
 
 // ------------------------------------------------------------------ K3
 template <int NX, int ROWS, typename TIN, typename TOUT>
@@ -341,21 +355,36 @@ __global__ __launch_bounds__(NT) void k_row_inv(const TIN* __restrict__ in, TOUT
   __shared__ float2 tw[tw_size(NX) > 0 ? tw_size(NX) : 1];
   const int tid = threadIdx.x;
   const long base = ((long)blockIdx.y * ny + (long)blockIdx.x * ROWS) * NX;
+  Tile<NX, ROWS, TIN> tile;
+  tile.load(in + base, tid);
   fill_twiddles<NX>(tw, tid, NT);
-  load_tile<NX, ROWS * NX>(buf, in + base, tid);
   __syncthreads();
-  fft_lds<NX, ROWS, NT, +1>(buf, tw, tid);
-  for (int q = tid; q < ROWS * NX; q += NT)
-    store_c(out + base + q, c2::scale(buf[(q / NX) * S + skew(q % NX)], scale));
+  tile.put(buf, tid);
+  tile_ready<NX, ROWS, NT>();
+  fft_tile<NX, ROWS, NT, +1>(buf, tw, tid);
+  // a wave writes the rows it transformed
+#pragma unroll
+  for (int i = 0; i < tile_slots<NX, ROWS, NT>(); ++i) {
+    int b, x;
+    if (tile_element<NX, ROWS, NT>(tid, i, &b, &x))
+      store_c(out + base + b * NX + x, c2::scale(buf[b * S + place<NX>(x)], scale));
+  }
 }
 
 // Workgroups go to the 8 XCDs round-robin by linear index.  The tiles of a
-// frame below write runs of 8 or 16 values, so neighbouring tiles 2m and
-// 2m + 1 share 128-byte lines; when the tile count is a multiple of 16 this
-// numbering gives the two of a pair indices of one residue mod 8 (one XCD,
-// one L2), where the partial lines merge before they reach HBM.
-__device__ inline int xcd_paired(int bx, int tiles) {
-  return (tiles & 15) ? bx : 16 * (bx >> 4) + 2 * (bx & 7) + ((bx >> 3) & 1);
+// frame below write runs of 4 to 32 values per row, so neighbouring tiles share
+// 128-byte lines (or neighbouring lines); this numbering gives each run of XG
+// tiles indices of one residue mod 8 (one XCD, one L2), where partial lines
+// merge and longer runs collect before they reach HBM.  Column passes of 2^26
+// FP32 pixels: 512^2 239 us with XG = 1, 238 with 2, 236 with 4, 207 with 8;
+// 1024^2 275, 249, 229, 224; 1280^2 515, 385, 342, 337; fp16 passes need 2 (239,
+// 147, 148, 146 at 1024^2) and gain no more.
+constexpr int XG = 8;
+__device__ inline void xcd_tile(int* tile, long* frame) {
+  const unsigned tiles = gridDim.x, total = gridDim.x * gridDim.y, lin = blockIdx.y * tiles + blockIdx.x;
+  const unsigned q = lin < total / (8 * XG) * (8 * XG) ? lin / (8 * XG) * (8 * XG) + lin % 8 * XG + lin / 8 % XG : lin;
+  *tile = q % tiles;
+  *frame = q / tiles;
 }
 
 // ------------------------------------------------------------------ K4 rows / complex rows
@@ -369,38 +398,41 @@ __global__ __launch_bounds__(NT) void k_rows_c2c(const TIN* __restrict__ in, TOU
   __shared__ float2 buf[ROWS * S];
   __shared__ float2 tw[tw_size(NX) > 0 ? tw_size(NX) : 1];
   const int tid = threadIdx.x;
-  const int y0 = xcd_paired(blockIdx.x, gridDim.x) * ROWS;
-  const long t = blockIdx.y;
-  fill_twiddles<NX>(tw, tid, NT);
+  int tile_x;
+  long t;
+  xcd_tile(&tile_x, &t);
+  const int y0 = tile_x * ROWS;
   const TIN* src = in + (t * ny + y0) * (long)NX;
   // Runs of 8 values; every run of the tile is loaded before the first LDS
   // write.
-  constexpr int E8 = ROWS * (NX / 8), PER = (E8 + NT - 1) / NT;
+  constexpr int PER = tile_slots<NX / 8, ROWS, NT>();
   float2 v[PER][8];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int q = tid + k * NT;
-    if (E8 % NT == 0 || q < E8) load8c(src + (q / (NX / 8)) * NX + 8 * (q % (NX / 8)), v[k]);
+    int r, c;
+    if (tile_element<NX / 8, ROWS, NT>(tid, k, &r, &c)) load8c(src + r * NX + 8 * c, v[k]);
   }
+  fill_twiddles<NX>(tw, tid, NT);
+  __syncthreads();
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int q = tid + k * NT;
-    if (E8 % NT != 0 && q >= E8) continue;
-    const int r = q / (NX / 8), c = q % (NX / 8);
+    int r, c;
+    if (!tile_element<NX / 8, ROWS, NT>(tid, k, &r, &c)) continue;
     if (qx) {
       const float2 cy = qy[y0 + r];
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[k][e] = c2::mul(v[k][e], c2::mul(qx[8 * c + e], cy));
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) buf[r * S + skew(8 * c + e)] = v[k][e];
+    for (int e = 0; e < 8; ++e) buf[r * S + place<NX>(8 * c + e)] = v[k][e];
   }
+  tile_ready<NX, ROWS, NT>();
+  fft_tile<NX, ROWS, NT, DIR>(buf, tw, tid);
   __syncthreads();
-  fft_lds<NX, ROWS, NT, DIR>(buf, tw, tid);
   TOUT* dst = out + t * (long)NX * ny + y0;
   for (int q = tid; q < NX * ROWS; q += NT) {
     const int p = q / ROWS, r = q % ROWS;
-    store_c(dst + (long)p * ny + r, c2::scale(buf[r * S + skew(p)], scale));
+    store_c(dst + (long)p * ny + r, c2::scale(buf[r * S + place<NX>(p)], scale));
   }
 }
 
@@ -414,39 +446,47 @@ __global__ __launch_bounds__(NT) void k_col_full(const TIO* __restrict__ in, TIO
   __shared__ float2 buf[BC * S];
   __shared__ float2 tw[tw_size(NY) > 0 ? tw_size(NY) : 1];
   const int tid = threadIdx.x;
-  const int p0 = xcd_paired(blockIdx.x, gridDim.x) * BC;
-  const long t = blockIdx.y;
-  fill_twiddles<NY>(tw, tid, NT);
+  int tile_x;
+  long t;
+  xcd_tile(&tile_x, &t);
+  const int p0 = tile_x * BC;
   const TIO* src = in + (t * nx + p0) * (long)NY;
-  load_tile<NY, BC * NY>(buf, src, tid);
+  Tile<NY, BC, TIO> tile;
+  tile.load(src, tid);
   // The tile's transfer-function values are one contiguous run
   // ht[p0 * NY + q], fetched here so they arrive during the forward FFT.
   // For 1024-point columns the extra registers would cost the second
   // workgroup per CU, so there they are read after the FFT.
-  constexpr int E = BC * NY, PER = (E + NT - 1) / NT;
+  constexpr int PER = tile_slots<NY, BC, NT>();
   constexpr bool PRE = NY < 1024;
   const float2* hp = ht + (long)p0 * NY;
   float2 h[PRE ? PER : 1];
   if constexpr (PRE) {
 #pragma unroll
-    for (int k = 0; k < PER; ++k)
-      if (E % NT == 0 || tid + k * NT < E) h[k] = hp[tid + k * NT];
+    for (int k = 0; k < PER; ++k) {
+      int b, y;
+      if (tile_element<NY, BC, NT>(tid, k, &b, &y)) h[k] = hp[b * NY + y];
+    }
   }
+  fill_twiddles<NY>(tw, tid, NT);
   __syncthreads();
-  fft_lds<NY, BC, NT, -1>(buf, tw, tid);
+  tile.put(buf, tid);
+  tile_ready<NY, BC, NT>();
+  fft_tile<NY, BC, NT, -1>(buf, tw, tid);
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int q = tid + k * NT;
-    if (E % NT != 0 && q >= E) continue;
-    float2* e = &buf[(q / NY) * S + skew(q % NY)];
-    *e = c2::mul(*e, PRE ? h[PRE ? k : 0] : hp[q]);
+    int b, y;
+    if (!tile_element<NY, BC, NT>(tid, k, &b, &y)) continue;
+    float2* e = &buf[b * S + place<NY>(y)];
+    *e = c2::mul(*e, PRE ? h[PRE ? k : 0] : hp[b * NY + y]);
   }
+  tile_ready<NY, BC, NT>();
+  fft_tile<NY, BC, NT, +1>(buf, tw, tid);
   __syncthreads();
-  fft_lds<NY, BC, NT, +1>(buf, tw, tid);
   TIO* dst = out + t * (long)NY * nx;
   for (int q = tid; q < BC * NY; q += NT) {
     const int y = q / BC, i = q % BC;
-    store_c(dst + (long)y * nx + p0 + i, buf[i * S + skew(y)]);
+    store_c(dst + (long)y * nx + p0 + i, buf[i * S + place<NY>(y)]);
   }
 }
 
@@ -459,11 +499,13 @@ __global__ __launch_bounds__(NT) void k_fresnel_cols(const TIN* __restrict__ in,
   __shared__ float2 buf[BC * S];
   __shared__ float2 tw[tw_size(NY) > 0 ? tw_size(NY) : 1];
   const int tid = threadIdx.x;
-  const int p0 = xcd_paired(blockIdx.x, gridDim.x) * BC;
-  const long t = blockIdx.y;
-  fill_twiddles<NY>(tw, tid, NT);
+  int tile_x;
+  long t;
+  xcd_tile(&tile_x, &t);
+  const int p0 = tile_x * BC;
   const TIN* src = in + (t * nx + p0) * (long)NY;
-  load_tile<NY, BC * NY>(buf, src, tid);
+  Tile<NY, BC, TIN> tile;
+  tile.load(src, tid);
   // Output element q = tid + k * NT is (y, i) = (q / BC, q % BC); NT is a
   // multiple of BC, so each thread keeps one column i and steps y by NT / BC.
   // Its chirp values are fetched here and arrive during the FFT.
@@ -475,14 +517,18 @@ __global__ __launch_bounds__(NT) void k_fresnel_cols(const TIN* __restrict__ in,
 #pragma unroll
   for (int k = 0; k < PER; ++k)
     if (E % NT == 0 || yt + k * YS < NY) cy[k] = qy[yt + k * YS];
+  fill_twiddles<NY>(tw, tid, NT);
   __syncthreads();
-  fft_lds<NY, BC, NT, DIR>(buf, tw, tid);
+  tile.put(buf, tid);
+  tile_ready<NY, BC, NT>();
+  fft_tile<NY, BC, NT, DIR>(buf, tw, tid);
+  __syncthreads();
   TOUT* dst = out + t * (long)NY * nx + p0 + i;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int y = yt + k * YS;
     if (E % NT != 0 && y >= NY) continue;
-    float2 v = c2::mul(buf[i * S + skew(y)], c2::mul(cx, cy[k]));
+    float2 v = c2::mul(buf[i * S + place<NY>(y)], c2::mul(cx, cy[k]));
     store_c(dst + (long)y * nx, c2::scale(v, scale));
   }
 }
