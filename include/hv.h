@@ -128,7 +128,10 @@ hv_status hv_ctx_set_chunk_frames(hv_ctx* ctx, int frames);
  * propagated ("band first"), which transforms nb fields per window instead
  * of W frames.
  *   HV_ORDER_FRAMES_FIRST the paper's order and the default: every frame is
- *                         propagated, then the temporal transform;
+ *                         propagated, then the temporal transform (where the
+ *                         two are fused, the last pass of the propagation, the
+ *                         inverse transform along x, follows the transform
+ *                         along t inside one kernel, on the band's bins);
  *   HV_ORDER_AUTO         band first where it moves fewer bytes per window
  *                         and the shape is supported (u8/u16 frames, nx a
  *                         power of two in [64, 512], ny 64, 128, 256, 320,

@@ -204,24 +204,6 @@ static hv_status build_dft_plan(size_t* held, DftPlan& p) {
     if ((m & 1) == 0) return (k & 1) == 0 ? cs : sn;
     return (k & 1) == 0 ? -sn : cs;
   };
-  std::vector<float> a32((size_t)mt * w * 64);
-  for (int m_t = 0; m_t < mt; ++m_t)
-    for (int kk = 0; kk < w; ++kk)
-      for (int lane = 0; lane < 64; ++lane)
-        a32[((size_t)m_t * w + kk) * 64 + lane] = (float)coef(32 * m_t + (lane & 31), 2 * kk + (lane >> 5));
-  std::vector<hv_h8> hi((size_t)mt * (w / 8) * 64), lo(hi.size());
-  for (int m_t = 0; m_t < mt; ++m_t)
-    for (int kk = 0; kk < w / 8; ++kk)
-      for (int lane = 0; lane < 64; ++lane) {
-        hv_h8 h, l;
-        for (int e = 0; e < 8; ++e) {
-          const float a = (float)coef(32 * m_t + (lane & 31), 16 * kk + 8 * (lane >> 5) + e);
-          h[e] = (_Float16)a;
-          l[e] = (_Float16)(a - (float)h[e]);
-        }
-        hi[((size_t)m_t * (w / 8) + kk) * 64 + lane] = h;
-        lo[((size_t)m_t * (w / 8) + kk) * 64 + lane] = l;
-      }
   std::vector<float> wts((size_t)3 * mt * 16, 0.f);
   for (int b = 0; b < nb; ++b) {
     wts[b] = 1.0f;
@@ -256,11 +238,8 @@ static hv_status build_dft_plan(size_t* held, DftPlan& p) {
   }
   hv_status st = p.wk.upload(wk.data(), wk.size() * sizeof(float), held);
   if (!st) st = p.index.upload(index.data(), index.size() * sizeof(int), held);
-  if (!st) st = p.a32.upload(a32.data(), a32.size() * sizeof(float), held);
   if (!st) st = p.ar_hi.upload(rhi.data(), rhi.size() * sizeof(hv_h8), held);
   if (!st) st = p.ar_lo.upload(rlo.data(), rlo.size() * sizeof(hv_h8), held);
-  if (!st) st = p.a16hi.upload(hi.data(), hi.size() * sizeof(hv_h8), held);
-  if (!st) st = p.a16lo.upload(lo.data(), lo.size() * sizeof(hv_h8), held);
   if (!st) st = p.wts.upload(wts.data(), wts.size() * sizeof(float), held);
   return st;
 }
@@ -898,7 +877,7 @@ static hv_status stft_band_first(Ctx* ctx, const void* in, int in_t, int ny, int
 // call (frames from j0 * stride), spatial passes then the temporal GEMM with
 // the moment epilogue; outputs at window j0 of m0/m1/m2/spec.
 static hv_status frames_first_chunk(Ctx* ctx, const void* in, int in_t, int ny, int nx, const hv_optics& o,
-                                    const CoefGemm& g, const FieldBand& band, int nb, int w, int stride, int j0, int g_n, bool mixed,
+                                    const FieldBand& band, int nb, int w, int stride, int j0, int g_n, bool mixed,
                                     float* m0, float* m1, float* m2, float2* spec, hipStream_t st,
                                     const FixedWs* fixed) {
   hv_status s;
@@ -910,17 +889,13 @@ static hv_status frames_first_chunk(Ctx* ctx, const void* in, int in_t, int ny, 
   float* o1 = m1 ? m1 + (size_t)j0 * frame : nullptr;
   float* o2 = m2 ? m2 + (size_t)j0 * frame : nullptr;
   float2* os = spec ? spec + (size_t)j0 * nb * frame : nullptr;
-  const bool fused = o.method == HV_AS && rowinv_coef_fits(nx, w);
+  const bool fused = o.method == HV_AS && row_band_fits(nx, w, stride, nb, mixed);
   SpatialOut so;
   if ((s = spatial(ctx, src, in_t, nf, ny, nx, o, mixed, !fused, fsc, st, so, fixed))) return s;
-  if (fused) {
-    // B = z_to_field * IDFT_x(z) * bsc with bsc keeping fp16 in range
-    const float bsc = mixed ? so.z_to_field * fsc : 1.f;
-    const float amp = mixed ? 1.f / fsc : so.z_to_field;
+  if (fused)
     return run(ctx, "rowinv_coef", st, fixed, [&] {
-      return launch_rowinv_coef(so.z, so.half, ny, nx, stride, g_n, g, mixed, bsc, amp, o0, o1, o2, os, st);
+      return launch_row_band(so.z, so.half, ny, nx, stride, g_n, band, so.z_to_field, o0, o1, o2, os, st);
     });
-  }
   return run(ctx, "field_coef", st, fixed, [&] {
     return launch_field_dft(so.f, so.half, (long)frame, stride, g_n, band, nullptr, 0, w - 1, 1.f / so.f_scale, o0,
                             o1, o2, os, st);
@@ -968,8 +943,6 @@ static hv_status stft_impl(hv_ctx* ctx, const void* in, int in_t, int n, int ny,
   const bool mixed = prec == HV_PREC_MIXED;
   const size_t frame = (size_t)ny * nx;
   hipStream_t st = (hipStream_t)hip_stream;
-  CoefGemm g{w, dp->mtiles, (int)dp->bins.size(), (const float*)dp->a32.ptr, (const hv_h8*)dp->a16hi.ptr,
-             (const hv_h8*)dp->a16lo.ptr, (const float*)dp->wts.ptr, 3};
   const int nb = (int)dp->bins.size();
   if (!optics) {
     return launch_field_dft(in, false, (long)frame, stride, nwin_total, dp->band(), nullptr, 0, w - 1, 1.f, m0, m1,
@@ -1002,7 +975,7 @@ static hv_status stft_impl(hv_ctx* ctx, const void* in, int in_t, int n, int ny,
   for (int j0 = 0, c = 0; j0 < nwin_total && res == HV_OK; j0 += gw, ++c) {
     st = (l2 && (c & 1)) ? l2->s : caller;
     const int g_n = nwin_total - j0 < gw ? nwin_total - j0 : gw;
-    res = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, g, dp->band(), nb, w, stride, j0, g_n, mixed, m0, m1, m2, spec, st,
+    res = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, dp->band(), nb, w, stride, j0, g_n, mixed, m0, m1, m2, spec, st,
                              nullptr);
   }
   if (l2) {  // join, also after an error, so no work of this call outlives it on the second stream
@@ -1048,8 +1021,6 @@ hv_status hv_stft_moments_noalloc(hv_ctx* ctx, const void* in, int in_t, int n, 
   const bool mixed = prec == HV_PREC_MIXED;
   const size_t frame = (size_t)ny * nx;
   hipStream_t st = (hipStream_t)hip_stream;
-  CoefGemm g{w, dp->mtiles, (int)dp->bins.size(), (const float*)dp->a32.ptr, (const hv_h8*)dp->a16hi.ptr,
-             (const hv_h8*)dp->a16lo.ptr, (const float*)dp->wts.ptr, 3};
   const int nb = (int)dp->bins.size();
   if (!optics) {  // a field in memory: the temporal kernel alone, no workspace
     return launch_field_dft(in, false, (long)frame, stride, nwin_total, dp->band(), nullptr, 0, w - 1, 1.f, m0, m1,
@@ -1062,7 +1033,7 @@ hv_status hv_stft_moments_noalloc(hv_ctx* ctx, const void* in, int in_t, int n, 
   const size_t cplx = mixed ? 4 : 8;
   const bool as = optics->method == HV_AS;
   const bool real_rows = as && in_t != HV_C64 && pow2_in(nx, 64, 1024) && pow2_in(ny, 64, 1024);
-  const bool fused = as && rowinv_coef_fits(nx, w);
+  const bool fused = as && no_field_workspace(nx, w);
   const size_t per[3] = {real_rows ? frame / 2 * cplx : frame * cplx, as ? frame * cplx : 0,
                          fused ? 0 : frame * cplx};
   const size_t per_frame = per[0] + per[1] + per[2];
@@ -1087,7 +1058,7 @@ hv_status hv_stft_moments_noalloc(hv_ctx* ctx, const void* in, int in_t, int n, 
   }
   for (int j0 = 0; j0 < nwin_total; j0 += gw) {
     const int g_n = nwin_total - j0 < gw ? nwin_total - j0 : gw;
-    if ((s = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, g, dp->band(), nb, w, stride, j0, g_n, mixed, m0, m1, m2,
+    if ((s = frames_first_chunk(ctx, in, in_t, ny, nx, *optics, dp->band(), nb, w, stride, j0, g_n, mixed, m0, m1, m2,
                                 nullptr, st, &fx)))
       return s;
   }

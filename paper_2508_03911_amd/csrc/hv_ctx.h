@@ -50,11 +50,13 @@ struct DftPlan {
   int window = 0, mtiles = 0;
   std::vector<int> bins;
   std::vector<double> freqs;
-  DevBuf a32, a16hi, a16lo, wts;
+  DevBuf wts;          // [3][16 mtiles]: 1, f, f^2 in band order
   uint64_t mask = 0;   // bit k: bin k belongs to the band
   DevBuf wk, index;    // [2][W] f_k, f_k^2 by bin; [W] place of bin k in the band
   FieldBand band() const {
-    return {window, (int)bins.size(), mask, (const float*)wk.ptr, (const int*)index.ptr};
+    const float* w = (const float*)wts.ptr;
+    return {window, (int)bins.size(), mask, (const float*)wk.ptr, (const int*)index.ptr, w + 16 * mtiles,
+            w + 32 * mtiles};
   }
   // real-input fragments for the band-first order: A[2b + c][t] =
   // (cos, -sin)(2 pi k_b t / W), [mtiles][max(1, W/16)][64] fp16x8 (hi, lo)

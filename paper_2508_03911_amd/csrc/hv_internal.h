@@ -69,13 +69,6 @@ struct CoefGemm {
   int nout;            // outputs written (1..3)
 };
 
-// Fused: row inverse FFT of W frames of one row, then the coefficient GEMM
-// and weighted power epilogue.  z: chunk [nf][ny][nx]; window jj starts at
-// frame jj*stride of the chunk.  Outputs out[k] + jj*ny*nx + y*nx + x.
-hv_status launch_rowinv_coef(const void* z, bool half_in, int ny, int nx, int stride, int nwin,
-                             const CoefGemm& g, bool mixed, float b_scale, float out_scale, float* out0,
-                             float* out1, float* out2, float2* spec, hipStream_t st);
-
 // The band of a DFT plan for the kernels that transform a pixel's samples in
 // registers.
 struct FieldBand {
@@ -84,7 +77,20 @@ struct FieldBand {
   uint64_t mask;     // bit k: bin k belongs to it
   const float* wk;   // [2][W]: f_k and f_k^2 (0 outside the band)
   const int* index;  // [W]: place of bin k in the band
+  const float* f1;   // [npair]: f and f^2 of the bins in band order
+  const float* f2;
 };
+
+// From the column pass's output z [nf][ny][nx] (window jj from frame
+// jj*stride): temporal transform, inverse row transform of the band's bins,
+// moments and bins as launch_field_dft, amplitudes * amp.
+// row_band_fits: taken for this shape and band, rather than the field in memory
+// (the same for every caller); always so for the shapes whose moments path
+// reserves no field workspace.
+bool no_field_workspace(int nx, int window);
+bool row_band_fits(int nx, int window, int stride, int nb, bool half);
+hv_status launch_row_band(const void* z, bool half_in, int ny, int nx, int stride, int nwin, const FieldBand& b,
+                          float amp, float* out0, float* out1, float* out2, float2* spec, hipStream_t st);
 
 // Field chunk [nf][P] (P = ny*nx) in memory, one lane per pixel: moments and
 // band bins (spec, nullable) of the window, amplitudes * amp.  With vec
@@ -100,7 +106,6 @@ bool field_energy_fits(bool half_in, int window, int c1, int c2);
 hv_status launch_field_energy(const void* u, bool half_in, long npix, int stride, int nwin, int window,
                               const float2* vec, int c1, int c2, float amp, float* m0, hipStream_t st);
 
-bool rowinv_coef_fits(int nx, int window);
 
 // ---------------------------------------------------------------- PCA kernels
 

@@ -282,7 +282,7 @@ hv_status hv_stream_open(hv_ctx* ctx, int ny, int nx, int raw_t, const hv_optics
   // workspace of one launch of `group` windows: spectra (and a field when not fused)
   const size_t nf = (size_t)(group - 1) * s + w;
   const size_t cplx = prec == HV_PREC_MIXED ? 4 : 8;
-  const bool fused = optics->method == HV_AS && rowinv_coef_fits(nx, w);
+  const bool fused = optics->method == HV_AS && no_field_workspace(nx, w);
   const size_t ws0 = nf * npix * cplx;  // row pass output (upper bound)
   size_t ws1 = nf * npix * cplx;
   if (optics->method == HV_AS && band_first_fits(ny, nx, raw_t)) {

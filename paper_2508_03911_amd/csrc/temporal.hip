@@ -1,17 +1,15 @@
-// Temporal transforms on MFMA: the short-time DFT as a dense GEMM with a
-// Doppler-moment epilogue, and the PCA projection energy, which has the same
-// shape (Sec. III-B.1: temporal transform over a window of consecutive
-// reconstructed frames, then a moment over a range of temporal indices).
+// Temporal transforms on MFMA: the covariance of PCA and SSA, the projection
+// energy and the SSA moments over ranges that neither keep nor leave out few
+// components (field.hip has the others), as dense GEMMs with a weighted-power
+// epilogue; and the full-band STFT of long windows (Sec. III-B.1).
 //
 // A window of W frames at P pixels is read as the real matrix
 // B [2W x P] with row 2t + c = component c (0 real, 1 imaginary) of frame t.
 // A coefficient matrix A [2M x 2W] whose rows come in (real, imaginary)
-// pairs turns B into M complex outputs per pixel:
-//   DFT:  pair b is bin k_b: Re = sum_t (ur cos + ui sin), Im = sum_t
-//         (ui cos - ur sin) with angle 2 pi k_b t / W;
-//   PCA:  pair c is component c: Y_c = sum_t X_t V[t, c].
-// The epilogue forms |.|^2 of every pair and sums them with up to three
-// weight vectors (f^0, f^1, f^2 for the moments; 1 for the PCA energy).
+// pairs turns B into M complex outputs per pixel (PCA: component c, Y_c =
+// sum_t X_t V[t, c]; SSA: a bin of the filtered window).  The epilogue forms
+// |.|^2 of every pair and sums them with up to three weight vectors (f^0, f^1,
+// f^2 for the moments; 1 for the PCA energy).
 //
 // MFMA layouts (gfx950, wave64).  v_mfma_f32_32x32x2f32: lane l holds
 // A[l%32][k0 + l/32] and B[k0 + l/32][l%32].  v_mfma_f32_32x32x16_f16: lane l
@@ -26,7 +24,6 @@
 #include "hv_internal.h"
 
 using namespace hvk;
-using hvi::persistent_grid;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -98,11 +95,10 @@ struct CoefArgs {
   const hv_h8* a16lo;
   long a_win_stride;  // elements of a32 (and of a16) per window; 0 = shared
   const float* wts;   // [3][mtiles*16]
-  int mtiles, npair, nout;
+  int mtiles, nout;
   float bsc;          // scale applied to B before the fp16 split
   float amp;          // scale applied to every output amplitude
   float* out[3];
-  float2* spec;       // [nwin][npair][npix] or null
 };
 
 template <int W, bool MIXED>
@@ -123,48 +119,30 @@ __device__ inline void load_afrag(AFrag<W, MIXED>& f, const CoefArgs& g, long jj
 }
 
 // GEMM + epilogue for the wave's pixel tile [x0, x0+32) of the LDS tile.
-// Writes outputs at out[k][obase + x0 + lane] and spec[(jj*npair + pair)*npix + obase + x0 + lane].
-// PRE: f0 holds the fragments of tile 0, loaded by the caller; otherwise
-// every tile's fragments are loaded here.
-// PIPE (with PRE): the next tile's fragments are loaded into a second set of
-// registers before the current tile's MFMAs, so their latency hides behind
-// them (W more VGPRs: for kernels with registers to spare).
-template <int W, bool MIXED, bool EXACT_B, bool PRE, bool PIPE = false>
+// Writes outputs at out[k][obase + x0 + lane].  `cur` holds the fragments of
+// tile 0, loaded by the caller; the next tile's fragments are loaded into a second
+// set of registers before the current tile's MFMAs, so their latency hides
+// behind them.
+template <int W, bool MIXED, bool EXACT_B>
 __device__ inline void coef_pixels(const CoefArgs& g, const float* wts_lds, const float2* buf, int S, int x0,
-                                   int lane, long jj, long obase, long npix, const AFrag<W, MIXED>& f0) {
-  static_assert(!PIPE || PRE, "the pipelined form starts from the caller's first fragments");
+                                   int lane, long jj, long obase, long npix, AFrag<W, MIXED> cur) {
   const int h = lane >> 5;
   float e0 = 0.f, e1 = 0.f, e2 = 0.f;
-  AFrag<W, MIXED> cur;
-  if constexpr (PIPE) cur = f0;
   for (int mt = 0; mt < g.mtiles; ++mt) {
-    f32x16 acc;
-    if constexpr (PIPE) {
-      AFrag<W, MIXED> nxt;
-      if (mt + 1 < g.mtiles) load_afrag(nxt, g, jj, mt + 1, lane);
-      acc = coef_tile<W, MIXED, EXACT_B>(cur, buf, S, x0, lane, g.bsc);
-      cur = nxt;
-    } else if (PRE && mt == 0) {
-      acc = coef_tile<W, MIXED, EXACT_B>(f0, buf, S, x0, lane, g.bsc);
-    } else {
-      AFrag<W, MIXED> f;
-      load_afrag(f, g, jj, mt, lane);
-      acc = coef_tile<W, MIXED, EXACT_B>(f, buf, S, x0, lane, g.bsc);
-    }
+    AFrag<W, MIXED> nxt;
+    if (mt + 1 < g.mtiles) load_afrag(nxt, g, jj, mt + 1, lane);
+    const f32x16 acc = coef_tile<W, MIXED, EXACT_B>(cur, buf, S, x0, lane, g.bsc);
+    cur = nxt;
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
-        const int pair = 16 * mt + 4 * gq + 2 * h + p;
         const float re = acc[4 * gq + 2 * p], im = acc[4 * gq + 2 * p + 1];
         const float pw = re * re + im * im;
         const int wi = 16 * mt + 4 * gq + 2 * h + p;
         e0 += wts_lds[wi] * pw;
         e1 += wts_lds[MT_MAX * 16 + wi] * pw;
         e2 += wts_lds[2 * MT_MAX * 16 + wi] * pw;
-        if (g.spec && pair < g.npair)
-          g.spec[(jj * g.npair + pair) * npix + obase + x0 + (lane & 31)] =
-              make_float2(re * g.amp, im * g.amp);
       }
     }
   }
@@ -184,85 +162,6 @@ __device__ inline void load_wts(float* wts_lds, const CoefArgs& g, int tid, int 
   for (int i = tid; i < 3 * MT_MAX * 16; i += nthreads) {
     const int k = i / (MT_MAX * 16), m = i % (MT_MAX * 16);
     wts_lds[i] = (m < g.mtiles * 16 && k < g.nout) ? g.wts[k * g.mtiles * 16 + m] : 0.f;
-  }
-}
-
-// ------------------------------------------------------------------ fused row inverse + GEMM
-// Unit u = (window u / ny, row u % ny): the W rows y of the window's frames
-// are inverse-transformed in LDS and reduced by the coefficient GEMM.
-//
-// FP16 input: persistent blocks with a register prefetch of the next unit's
-// rows (16 VGPRs) while the current unit is transformed and reduced.
-// FP32 input: one unit per block.  A 32-VGPR prefetch would lift the kernel
-// past 128 VGPRs and halve the resident blocks per CU, which costs more than
-// the prefetch gains (measured at 256 x 256, W = 32).
-template <int NX, int W, bool MIXED, typename TIN>
-__global__ __launch_bounds__(NT) void k_rowinv_coef(const TIN* __restrict__ z, int ny, int stride, int nunits,
-                                                    CoefArgs g) {
-  constexpr bool PF = sizeof(TIN) == 4;
-  constexpr int S = lds_stride(NX);
-  __shared__ float2 buf[W * S];
-  __shared__ float2 tw[tw_size(NX) > 0 ? tw_size(NX) : 1];
-  __shared__ float wts_lds[3 * MT_MAX * 16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  fill_twiddles<NX>(tw, tid, NT);
-  load_wts(wts_lds, g, tid);
-  const long npix = (long)ny * NX;
-  // The row inverse FFT's first pass reads straight from registers: element
-  // (u, r) of this thread is frame b_u of the window at pixel i_u + r * SP
-  // (16 lanes take 16 consecutive pixels of one frame row), so the rows are
-  // loaded into exactly those registers and skip the LDS staging.
-  // (small tiles leave some threads without a first-pass butterfly)
-  constexpr int UF = fft_first_slots<NX, W, NT>(), RF = radix_of_pass(NX, 0), SP = NX / RF;
-  uint32_t po[UF];  // byte offset of element (u, 0) in the field (W * ny * NX * 8 B < 4 GiB)
-  bool act[UF];
-#pragma unroll
-  for (int u = 0; u < UF; ++u) {
-    int b, i;
-    act[u] = fft_first_index<NX, W, NT>(tid, u, 0, &b, &i);
-    po[u] = act[u] ? (uint32_t)(b * npix + i) * (uint32_t)sizeof(TIN) : 0u;
-  }
-  // first element of unit u = (window u / ny, row u % ny): wave-uniform
-  auto rows = [&](int u) { return z + (((long)(u / ny) * stride) * (long)ny + u % ny) * NX; };
-  auto load = [&](int u, TIN (&v)[UF][RF]) {
-    const TIN* src = rows(u);
-#pragma unroll
-    for (int uu = 0; uu < UF; ++uu)
-#pragma unroll
-      for (int r = 0; r < RF; ++r)
-        if (act[uu]) v[uu][r] = ld_off(src + r * SP, po[uu]);
-  };
-  // FP32 input: the A fragments are loaded before the FFT and consumed
-  // after it.  FP16 input: they are loaded in the GEMM (measured faster
-  // there: the 32 extra VGPRs across the FFT cost more than they hide).
-  auto reduce = [&](int u, const AFrag<W, MIXED>& af, const auto& src) {
-    fft_lds_io<NX, W, NT, +1>(buf, tw, tid, [&](int uu, int r, int, int) { return load_c(&src[uu][r]); }, nullptr);
-    for (int nt = wave; nt < NX / 32; nt += NT / 64)
-      coef_pixels<W, MIXED, false, !PF>(g, wts_lds, buf, S, nt * 32, lane, u / ny, (long)(u % ny) * NX, npix,
-                                        af);
-  };
-  if constexpr (PF) {
-    TIN pre[UF][RF];
-    int u = blockIdx.x;
-    if (u < nunits) load(u, pre);
-    for (; u < nunits; u += gridDim.x) {
-      TIN cur[UF][RF];
-#pragma unroll
-      for (int uu = 0; uu < UF; ++uu)
-#pragma unroll
-        for (int r = 0; r < RF; ++r) cur[uu][r] = pre[uu][r];
-      if (u + (int)gridDim.x < nunits) load(u + gridDim.x, pre);
-      AFrag<W, MIXED> unused;
-      reduce(u, unused, cur);
-      __syncthreads();
-    }
-  } else {
-    const int u = blockIdx.x;
-    TIN v[UF][RF];
-    load(u, v);
-    AFrag<W, MIXED> af;
-    load_afrag(af, g, u / ny, 0, lane);
-    reduce(u, af, v);
   }
 }
 
@@ -301,7 +200,7 @@ __global__ __launch_bounds__(NT) void k_field_coef(const TIN* __restrict__ u, lo
     for (int i = 0; i < BATCH; ++i) lds[RPI * (i0 + i) * S] = load_c(&v[i]);
   }
   __syncthreads();
-  coef_pixels<W, MIXED, EXACT, true, true>(g, wts_lds, buf, S, wave * 32, lane, jj, p0, npix, af);
+  coef_pixels<W, MIXED, EXACT>(g, wts_lds, buf, S, wave * 32, lane, jj, p0, npix, af);
 }
 
 // ------------------------------------------------------------------ full-band STFT power (temporal FFT)
@@ -694,7 +593,7 @@ hv_status launched(const char* what) {
 }
 
 CoefArgs make_args(const hvi::CoefGemm& g, long a_win_stride, float bsc, float amp, float* o0, float* o1,
-                   float* o2, float2* spec) {
+                   float* o2) {
   CoefArgs a;
   a.a32 = g.a32;
   a.a16hi = g.a16hi;
@@ -702,52 +601,13 @@ CoefArgs make_args(const hvi::CoefGemm& g, long a_win_stride, float bsc, float a
   a.a_win_stride = a_win_stride;
   a.wts = g.wts;
   a.mtiles = g.mtiles;
-  a.npair = g.npair;
   a.nout = g.nout;
   a.bsc = bsc;
   a.amp = amp;
   a.out[0] = o0;
   a.out[1] = o1;
   a.out[2] = o2;
-  a.spec = spec;
   return a;
-}
-
-template <int NX, int W, bool MIXED>
-hv_status go_rowinv(const void* z, bool half_in, int ny, int stride, int nwin, const CoefArgs& a,
-                    hipStream_t st) {
-  if constexpr (W * NX <= 8192 && (W * NX) % NT == 0) {
-    const int nunits = ny * nwin;
-    if (half_in) {
-      auto kern = k_rowinv_coef<NX, W, MIXED, hv_h2>;
-      hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, NT, nunits)), dim3(NT), 0, st, (const hv_h2*)z, ny, stride,
-                         nunits, a);
-    } else {
-      hipLaunchKernelGGL((k_rowinv_coef<NX, W, MIXED, float2>), dim3(nunits), dim3(NT), 0, st, (const float2*)z,
-                         ny, stride, nunits, a);
-    }
-    return launched("rowinv_coef");
-  } else {
-    return hvi::fail(HV_ERR_SHAPE, "fused row-inverse GEMM does not fit nx=%d W=%d", NX, W);
-  }
-}
-
-template <int W>
-hv_status go_rowinv_w(const void* z, bool half_in, int ny, int nx, int stride, int nwin, const CoefArgs& a,
-                      bool mixed, hipStream_t st) {
-  switch (nx) {
-    case 64: return mixed ? go_rowinv<64, W, true>(z, half_in, ny, stride, nwin, a, st)
-                          : go_rowinv<64, W, false>(z, half_in, ny, stride, nwin, a, st);
-    case 128: return mixed ? go_rowinv<128, W, true>(z, half_in, ny, stride, nwin, a, st)
-                           : go_rowinv<128, W, false>(z, half_in, ny, stride, nwin, a, st);
-    case 256: return mixed ? go_rowinv<256, W, true>(z, half_in, ny, stride, nwin, a, st)
-                           : go_rowinv<256, W, false>(z, half_in, ny, stride, nwin, a, st);
-    case 512: return mixed ? go_rowinv<512, W, true>(z, half_in, ny, stride, nwin, a, st)
-                           : go_rowinv<512, W, false>(z, half_in, ny, stride, nwin, a, st);
-    case 1024: return mixed ? go_rowinv<1024, W, true>(z, half_in, ny, stride, nwin, a, st)
-                            : go_rowinv<1024, W, false>(z, half_in, ny, stride, nwin, a, st);
-  }
-  return hvi::fail(HV_ERR_SHAPE, "nx=%d not supported", nx);
 }
 
 template <int W, bool MIXED>
@@ -775,24 +635,6 @@ void go_gram(const void* u, bool half_in, long npix, int stride, int nwin, long 
 }  // namespace
 
 namespace hvi {
-
-bool rowinv_coef_fits(int nx, int window) {
-  return (nx & (nx - 1)) == 0 && (long)nx * window <= 8192 && ((long)nx * window) % NT == 0;
-}
-
-hv_status launch_rowinv_coef(const void* z, bool half_in, int ny, int nx, int stride, int nwin, const CoefGemm& g,
-                             bool mixed, float b_scale, float out_scale, float* out0, float* out1, float* out2,
-                             float2* spec, hipStream_t st) {
-  if (nwin <= 0) return HV_OK;
-  CoefArgs a = make_args(g, 0, b_scale, out_scale, out0, out1, out2, spec);
-  switch (g.window) {
-    case 8: return go_rowinv_w<8>(z, half_in, ny, nx, stride, nwin, a, mixed, st);
-    case 16: return go_rowinv_w<16>(z, half_in, ny, nx, stride, nwin, a, mixed, st);
-    case 32: return go_rowinv_w<32>(z, half_in, ny, nx, stride, nwin, a, mixed, st);
-    case 64: return go_rowinv_w<64>(z, half_in, ny, nx, stride, nwin, a, mixed, st);
-  }
-  return fail(HV_ERR_SHAPE, "window %d not supported", g.window);
-}
 
 static hv_status field_coef(const void* u, bool half_in, long npix, int stride, int nwin, const CoefArgs& a,
                             int window, bool mixed, hipStream_t st) {
@@ -870,7 +712,7 @@ hv_status launch_coef_moments(const void* u, bool half_in, long npix, int stride
                               bool mixed, float b_scale, float out_scale, float* m0, float* m1, float* m2,
                               hipStream_t st) {
   CoefGemm g{window, mtiles, npair, a32, a16hi, a16lo, wts, 3};
-  CoefArgs a = make_args(g, (long)mtiles * window * 64, b_scale, out_scale, m0, m1, m2, nullptr);
+  CoefArgs a = make_args(g, (long)mtiles * window * 64, b_scale, out_scale, m0, m1, m2);
   return field_coef(u, half_in, npix, stride, nwin, a, window, mixed, st);
 }
 
@@ -879,7 +721,7 @@ hv_status launch_proj_energy(const void* u, bool half_in, long npix, int stride,
                              const float* wts, bool mixed, float b_scale, float out_scale, float* m0,
                              hipStream_t st) {
   CoefGemm g{window, mtiles, npair, a32, a16hi, a16lo, wts, 1};
-  CoefArgs a = make_args(g, (long)mtiles * window * 64, b_scale, out_scale, m0, nullptr, nullptr, nullptr);
+  CoefArgs a = make_args(g, (long)mtiles * window * 64, b_scale, out_scale, m0, nullptr, nullptr);
   return field_coef(u, half_in, npix, stride, nwin, a, window, mixed, st);
 }
 
