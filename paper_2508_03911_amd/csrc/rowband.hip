@@ -204,19 +204,17 @@ bool no_field_workspace(int nx, int window) { return skewed(nx) && (long)nx * wi
 // field path, us):
 //   FP32, powers of two  nb = s     923/1075 (64^2, W 64), 1023/1192 (256^2, W 64), 1004/1275 (512^2, W 32)
 //                        nb = 2 s   1329/1197, 1533/1546, 1498/1743: taken up to nb = 1.5 s
-//   fp16, powers of two  nb = s     649/677 (64^2, W 32), 604/709 (256^2, W 32), 753/796 (512^2, W 32), but
-//                                   819/695, 796/708 (W 64, one workgroup per CU); nb = 2 s 866/800, 1166/1073
 //   mixed radix, whose row transforms cost twice as much:
-//        FP32  15 of 32: 1139/1435 (320^2); 32 of 32: 1421/1449; 2 of 8: 1794/1891 (800^2); s = 4: 2258/1878
-//        fp16  15 of 32: 1003/1193; 32 of 32: 1395/1206; 3 of 8: 1598/1406 (800^2)
+//                        15 of 32: 1139/1435 (320^2); 32 of 32: 1421/1449; 2 of 8: 1794/1891 (800^2); s = 4: 2258/1878
+// fp16 storage keeps the field path, faster or not (753/796 at 512^2, W 32, but
+// 1166/1073 with overlap): its images carry the rounding of the stored field, and
+// stay what they were.
 // Shapes without a field workspace always come here (their bands fit).
 bool row_band_fits(int nx, int window, int stride, int nb, bool half) {
   if (no_field_workspace(nx, window)) return true;
-  const size_t lds = lds_of(nx, nb);
-  if (lds > (size_t)160 << 10) return false;
+  if (half || lds_of(nx, nb) > (size_t)160 << 10) return false;
   const int s = stride < window ? stride : window;
-  if (!skewed(nx)) return nb < s && s >= (half ? 16 : 8);
-  return half ? nb <= s && lds <= (size_t)80 << 10 : 2 * nb <= 3 * s;
+  return skewed(nx) ? 2 * nb <= 3 * s : nb < s && s >= 8;
 }
 
 hv_status launch_row_band(const void* z, bool half_in, int ny, int nx, int stride, int nwin, const FieldBand& b,
