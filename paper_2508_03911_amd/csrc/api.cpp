@@ -416,6 +416,29 @@ int Ctx::chunk_frames_for(int ny, int nx, bool mixed) const {
   return (int)f;
 }
 
+// Windows per chunk of the STFT paths.  The W - stride frames that a chunk
+// shares with the next are propagated in both, so where windows overlap a
+// chunk holds at least 16 times as many new frames, within about 1 GiB of
+// intermediates per stream (times of the moments call, us, with chunks of the
+// size below and with these: 1024x512 W 32 stride 16 1097 -> 884, 384^2 W 64
+// stride 16 6266 -> 2213, 256^2 W 32 stride 8 1039 -> 962; fp16 916 -> 743, 2505 ->
+// 1768, 839 -> 787).  Without overlap the size of chunk_frames_for, but no
+// fewer than its 96 MiB where that is 32 frames or more (512^2 FP32, 64 -> 32
+// frames: 1711 -> 1512; smaller launches lose at larger frames).
+int Ctx::chunk_windows(int ny, int nx, bool mixed, int w, int stride, int nwin) const {
+  const long per = (long)ny * nx * (mixed ? 4 : 8) * 3 / 2;
+  long f = chunk_frames_for(ny, nx, mixed);
+  if (chunk_frames <= 0 && (96L << 20) / per >= 32) f = std::min(f, (96L << 20) / per);
+  auto windows = [&](long frames) { return frames >= w ? (frames - w) / stride + 1 : 1L; };
+  long g = windows(f);
+  if (chunk_frames <= 0 && stride < w) {
+    g = std::max(g, std::min(16L * (w - stride) / stride + 1, windows((1L << 30) / per)));
+    const long chunks = (nwin + g - 1) / g;  // of even size
+    g = (nwin + chunks - 1) / chunks;
+  }
+  return (int)std::min<long>(g, nwin);
+}
+
 }  // namespace hvi
 
 using namespace hvi;
@@ -959,9 +982,7 @@ static hv_status stft_impl(hv_ctx* ctx, const void* in, int in_t, int n, int ny,
       return stft_band_first(ctx, in, in_t, ny, nx, *optics, *dp, w, stride, nwin_total, gb, mixed, m0, m1, m2,
                              spec, st, two_lanes);
   }
-  const int chunk = ctx->chunk_frames_for(ny, nx, mixed);
-  int gw = chunk >= w ? (chunk - w) / stride + 1 : 1;
-  if (gw < 1) gw = 1;
+  const int gw = ctx->chunk_windows(ny, nx, mixed, w, stride, nwin_total);
   // Chunks alternate between the caller's stream and a second one (per-kernel
   // timing events, when on, bracket each launch on its own stream and so
   // time it as it runs beside the other stream's work).
@@ -1087,8 +1108,7 @@ hv_status hv_stft_moments_host(hv_ctx* ctx, const void* host_in, int in_t, int n
   const bool mixed = prec == HV_PREC_MIXED;
   const int nwin_total = (n - w) / stride + 1;
   const size_t frame = (size_t)ny * nx, fbytes = frame * in_elem(in_t);
-  const int chunk = std::max(ctx->chunk_frames_for(ny, nx, mixed), w);
-  const int gw = (chunk - w) / stride + 1;
+  const int gw = ctx->chunk_windows(ny, nx, mixed, w, stride, nwin_total);
   const int cf = (gw - 1) * stride + w;  // frames staged per chunk
   hipStream_t st = (hipStream_t)hip_stream;
   float* const host_out[3] = {host_m0, host_m1, host_m2};
@@ -1170,8 +1190,7 @@ hv_status hv_stft_volume(hv_ctx* ctx, const void* in, int in_t, int n, int ny, i
     return timed(ctx, "time_fft", st, [&] {
       return launch_time_fft(in, false, (long)frame, stride, nwin_total, w, 1.f, power, st);
     });
-  const int chunk = std::max(ctx->chunk_frames_for(ny, nx, mixed), w);
-  const int gw = (chunk - w) / stride + 1;
+  const int gw = ctx->chunk_windows(ny, nx, mixed, w, stride, nwin_total);
   const float fsc = mixed ? fp16_field_scale(in_t, ny, nx) : 1.f;
   // chunks alternate between the caller's stream and a second one
   Ctx::Lane2* l2 = nullptr;

@@ -133,6 +133,7 @@ struct Ctx {
   DftPlan* dft_plan(const hv_temporal& tp, hv_status* st, bool build = true);
   DevBuf& work(hipStream_t s, int slot);
   int chunk_frames_for(int ny, int nx, bool mixed) const;
+  int chunk_windows(int ny, int nx, bool mixed, int w, int stride, int nwin) const;
 };
 
 // Runs f() (a kernel launch), bracketed by timing events when enabled.
