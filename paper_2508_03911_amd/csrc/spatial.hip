@@ -543,18 +543,29 @@ constexpr int p2floor(int r) {
   return p;
 }
 
-template <int NX, typename TIN, typename TOUT>
+// Calls of few 256-wide frames leave CUs without a 64-row tile; they take 16 rows
+// (8 frames of 256^2 8.9 -> 6.6 us with the event pair that times it, 32 frames 9.2
+// -> 7.7, 64 frames or 256 tiles 10.6/10.9).  Both give the same bits.
+template <int NX, typename TIN, typename TOUT, int DIV = 1>
 void go_r2c(const void* in, void* out, int n, int ny, float scale, hipStream_t st) {
-  constexpr int ROWS = cap64(16384 / NX);
+  constexpr int ROWS = cap64(16384 / NX) / DIV;
   const int nunits = n * (ny / ROWS);
+  if constexpr (NX == 256 && DIV == 1)
+    if (nunits < 256) return go_r2c<NX, TIN, TOUT, 4>(in, out, n, ny, scale, st);
   auto kern = k_row_r2c<NX, ROWS, TIN, TOUT>;
   hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, NT, nunits)), dim3(NT), 0, st, (const TIN*)in, (TOUT*)out, ny,
                      nunits, scale);
 }
 
+// Columns per tile: 16 of an FP32 frame 128 high, which fills the CUs sooner (whole
+// moments of 128 frames of 128^2 28.2 -> 28.6 us against 8 columns where that is best,
+// 32 columns 32.1; of 16384 frames 1245 us against 1337 of 8 and 1314 of 32).  The number of
+// frames does not enter: another tile's last bits differ, and a frame's bits must
+// not depend on its company.  fp16 storage, which would carry a last-bit
+// difference on, keeps 32, and a frame 64 high has no gain (512 wide: 635 us against 666).
 template <int NY, typename TIO>
 void go_col_as(const void* in, void* out, const float2* hs, int n, int nx, hipStream_t st) {
-  constexpr int BC = cap32(4096 / NY);  // nx/2 >= 32 >= BC, so BC divides nx/2
+  constexpr int BC = NY == 128 && sizeof(TIO) == 8 ? 16 : cap32(4096 / NY);  // divides nx/2 >= 32
   hipLaunchKernelGGL((k_col_as<NY, BC, TIO>), dim3((nx / 2) / BC * n), dim3(NT), 0, st, (const TIO*)in,
                      (TIO*)out, hs, nx, n % 8 == 0);
 }
