@@ -719,131 +719,187 @@ __global__ __launch_bounds__(256) void k_head_pooled(const float* __restrict__ p
   }
 }
 
+// A value at a wave-uniform base, which stays in scalar registers, and a 32-bit
+// byte offset per lane: without the hint a chain of 64-bit vector additions.
+__device__ inline __attribute__((address_space(1))) float& at_offset(const float* base, uint32_t bytes) {
+  typedef __attribute__((address_space(1))) char* gptr;
+  gptr p = (gptr)(uintptr_t)base;
+  asm("" : "+s"(p));
+  return *(__attribute__((address_space(1))) float*)(p + bytes);
+}
+
 // A 32-channel convolution of training as an implicit GEMM on the matrix
 // cores (FP32 operands, v_mfma_f32_32x32x2f32): per 16 x 16 output tile,
-// [256 pixels] x [288 = 9 c + tap] times [288] x [32 output channels], with
+// [32 output channels] x [288 = 9 c + tap] times [288] x [256 pixels], with
 // NCHW FP32 activations, in two modes:
 //   MODE 0 (forward):    out = ReLU(b + W * in)
-//   MODE 1 (input grad): out = W^T(flipped) * in, with in = dZ (the output
-//                        gradient already masked by the ReLU)
-// MODE 1 with relu_of (the activation A of the layer below): the stored
-// gradient is already taken through that layer's ReLU, out [A > 0].
-// Persistent: the layer's weights sit in LDS as B[k][o] for all of the
-// block's units; wave w owns the 32-pixel M tiles 2w and 2w + 1; the
-// outputs are staged in LDS so that each channel's 16-pixel rows are stored
-// contiguously.
+//   MODE 1 (input grad): out = W^T(flipped) * in [A > 0], with in = dZ (the
+//                        output gradient already masked by the ReLU) and A the
+//                        activation of the layer below, whose ReLU the stored
+//                        gradient is thereby taken through
+// Persistent: the layer's weights sit in LDS as A[k][o] for all of the
+// block's units; wave w owns the 32-pixel tiles 2w and 2w + 1, and a result
+// register is one channel of 32 neighbouring pixels, stored straight to its two
+// rows.  Bound by the matrix cores if nothing else takes their time, so a unit is
+// two phases of sixteen input channels (8 h .. and 16 + 8 h .., a step taking one
+// of either), and each phase's 72 steps carry, one a step, what the others need: the other half of the input tile on its way from
+// registers to LDS, the loads of the next unit's, the activations and the stores
+// of the unit before.
 template <int MODE>
 __global__ __launch_bounds__(256, 2) void k_conv_f32mfma(const float* __restrict__ in, const float* __restrict__ params,
                                                          int woff, int boff, float* __restrict__ out, int nunits,
-                                                         const float* __restrict__ relu_of) {
-  constexpr int K = NCH * 9, KH = K / 2;  // lanes 0-31 take k < 144, lanes 32-63 k >= 144
-  constexpr int XC = 18 * 19;              // floats per channel of the input tile
-  constexpr int OS = 257;                  // staging row stride
-  static_assert(NCH * OS <= NCH * XC, "output staging fits in the input tile");
-  static_assert(KH % 9 == 0, "each half of k holds whole channels");
-  __shared__ float xt[NCH][18][19];
+                                                         const float* __restrict__ act) {
+  constexpr int K = NCH * 9, HC = NCH / 2, STEPS = HC / 2 * 9;
+  constexpr int XC = 18 * 19;  // floats per channel of the input tile
+  // what a thread carries of half a tile: pixel tid of sixteen channels, pixel
+  // 256 + lane of the wave's four and pixel 320 + tid % 4 of channel tid / 4 (wave 0)
+  constexpr int NV = HC, NE = HC / 4, ITEMS = NV + NE + 1, NOUT = 32;
+  static_assert(ITEMS + NOUT <= STEPS, "one item a step");
+  __shared__ float xt[NCH * XC];
   __shared__ float wl[K * NCH];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, n = lane & 31, kb = lane >> 5;
-  for (int q = tid; q < K * NCH; q += 256) {
-    const int k = q / NCH, o = q % NCH, c = k / 9, tap = k % 9;
-    wl[q] = MODE == 0 ? params[woff + (o * NCH + c) * 9 + tap] : params[woff + (c * NCH + o) * 9 + (8 - tap)];
-  }
-  const float bias = MODE == 0 ? params[boff + n] : 0.f;
-  float* ot = &xt[0][0][0];
-  // per-lane bases: step ks reads k = ks + KH kb, i.e. channel ks / 9 + 16 kb
-  // and tap ks % 9, at offsets that are constants of ks
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, kb = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // result register r of lane l: output channel chan(r) + 4 (l / 32), pixel l % 32 of the tile
+  auto chan = [](int r) { return 8 * (r >> 2) + (r & 3); };
+  float bias[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) bias[r] = MODE == 0 ? params[boff + chan(r) + 4 * kb] : 0.f;
+  // channel i of half 0; half 1's are eight further
+  auto channel = [](int i) { return i % 8 + i / 8 * 16; };
+  // per-lane bases: step ks of phase h reads channel 8 h + ks / 9 + 16 kb and tap
+  // ks % 9, at offsets that are constants of ks
   const float* xa[2];
+  uint32_t at[2];  // bytes from the unit's corner to the lane's pixel of either tile
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt) {
     const int p = (2 * w + mt) * 32 + n;
-    xa[mt] = &xt[0][0][0] + kb * (KH / 9) * XC + (p >> 4) * 19 + (p & 15);
+    xa[mt] = xt + kb * HC * XC + (p >> 4) * 19 + (p & 15);
+    at[mt] = 4 * (4 * kb * HW + (p >> 4) * CROP + (p & 15));
   }
-  const float* wb = wl + kb * KH * NCH + n;
-  // the unit's input tile: every lane issues every load (clamped address,
-  // zeroed when stored to LDS)
-  constexpr int PER = (NCH * 324 + 255) / 256;
-  float v[PER];
-  uint64_t vmask = 0;
-  auto fetch = [&](int u) {
-    u = u < nunits ? u : nunits - 1;
-    const float* bp = in + (long)(u >> 4) * (NCH * HW);  // wave-uniform base, 32-bit lane offsets
-    const int ty0 = ((u & 15) >> 2) * 16, tx0 = (u & 3) * 16;
-    vmask = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int q = min(tid + 256 * i, NCH * 324 - 1);
-      const int c = q / 324, r = (q % 324) / 18, col = q % 18;
-      const int y = ty0 + r - 1, x = tx0 + col - 1;
-      vmask |= (uint64_t)(y >= 0 && y < CROP && x >= 0 && x < CROP) << i;
-      v[i] = bp[(c * CROP + min(max(y, 0), CROP - 1)) * CROP + min(max(x, 0), CROP - 1)];
-    }
+  const float* wb = wl + kb * HC * 9 * NCH + n;
+
+  // sources of the three kinds of items: byte offset in the image (clamped) and
+  // whether it is inside; the value is zeroed on its way to LDS if not
+  struct Source {
+    uint32_t v, e, t;
+    bool in_v, in_e, in_t;
   };
-  for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
-    const long b = u >> 4;
+  auto place = [](int pixel) { return pixel / 18 * 19 + pixel % 18; };
+  auto source = [&](int u) {
     const int ty0 = ((u & 15) >> 2) * 16, tx0 = (u & 3) * 16;
-    fetch(u);  // every load of the tile is issued before the first LDS write
-    __syncthreads();  // the previous unit's staged outputs are stored
+    auto of = [&](int pixel, bool& inside) {
+      const int y = ty0 + pixel / 18 - 1, x = tx0 + pixel % 18 - 1;
+      inside = y >= 0 && y < CROP && x >= 0 && x < CROP;
+      return (uint32_t)(4 * (min(max(y, 0), CROP - 1) * CROP + min(max(x, 0), CROP - 1)));
+    };
+    Source q;
+    q.v = of(tid, q.in_v);
+    q.e = of(256 + lane, q.in_e);
+    q.t = of(320 + (tid & 3), q.in_t) + 4 * HW * channel(lane >> 2);
+    return q;
+  };
+  auto load = [&](const float* half, int i, const Source& q) -> float {
+    if (i < NV) return at_offset(half + channel(i) * HW, q.v);
+    if (i < NV + NE) return at_offset(half + (channel(NE * w) + i - NV) * HW, q.e);
+    return at_offset(half, q.t);
+  };
+  float* pv = xt + place(tid);
+  float* pe = xt + place(256 + lane) + channel(NE * w) * XC;
+  float* pt = xt + place(320 + (tid & 3)) + channel(lane >> 2) * XC;
+  auto put = [&](int half, int i, float v, const Source& q) {
+    if (i < NV)
+      pv[(8 * half + channel(i)) * XC] = q.in_v ? v : 0.f;
+    else if (i < NV + NE)
+      pe[(8 * half + i - NV) * XC] = q.in_e ? v : 0.f;
+    else if (w == 0)
+      pt[8 * half * XC] = q.in_t ? v : 0.f;
+  };
+  auto corner = [](int u) { return (long)(u >> 4) * (NCH * HW) + ((u & 15) >> 2) * 16 * CROP + (u & 3) * 16; };
+  auto sample = [&](int u, int half) { return in + ((long)(u >> 4) * NCH + half * 8) * HW; };
+
+  int u = blockIdx.x;
+  if (u >= nunits) return;
+  float h0[ITEMS], h1[ITEMS], keep[NOUT], res[NOUT];
+  Source now = source(u);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int q = tid + 256 * i;
-      if (q < NCH * 324) xt[q / 324][(q % 324) / 18][q % 18] = (vmask >> i) & 1 ? v[i] : 0.f;
-    }
-    __syncthreads();
-    // the two 32-pixel products interleaved, operands read one step ahead
-    f32x16 acc[2];
+  for (int i = 0; i < ITEMS; ++i) h0[i] = load(sample(u, 0), i, now);
+  {  // the weights: every load issued before the first LDS write
+    float q[K * NCH / 256];
+    const int o = tid % NCH, c0 = tid / NCH * 4;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int i = 0; i < K * NCH / 256; ++i)
+      q[i] = params[woff + (MODE == 0 ? (o * NCH + c0) * 9 + i : ((c0 + i / 9) * NCH + o) * 9 + 8 - i % 9)];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+    for (int i = 0; i < ITEMS; ++i) h1[i] = load(sample(u, 1), i, now);
+#pragma unroll
+    for (int i = 0; i < K * NCH / 256; ++i) wl[(c0 * 9 + i) * NCH + o] = q[i];
+  }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) put(0, i, h0[i], now);
+
+  f32x16 acc[2];
+  // the 72 steps of a phase: the two 32-pixel products interleaved, operands read
+  // one step ahead, and `side` between them
+  auto phase = [&](int half, auto&& side) {
+    const float *x0 = xa[0] + 8 * half * XC, *x1 = xa[1] + 8 * half * XC, *wh = wb + 8 * half * 9 * NCH;
     auto xoff = [](int ks) { return (ks / 9) * XC + ((ks % 9) / 3) * 19 + (ks % 9) % 3; };
-    float a0 = xa[0][xoff(0)], a1 = xa[1][xoff(0)], bv = wb[0];
+    float a0 = x0[0], a1 = x1[0], bv = wh[0];
 #pragma unroll
-    for (int ks = 0; ks < KH; ++ks) {
+    for (int ks = 0; ks < STEPS; ++ks) {
       float a0n = 0.f, a1n = 0.f, bn = 0.f;
-      if (ks + 1 < KH) {
-        a0n = xa[0][xoff(ks + 1)];
-        a1n = xa[1][xoff(ks + 1)];
-        bn = wb[(ks + 1) * NCH];
+      if (ks + 1 < STEPS) {
+        a0n = x0[xoff(ks + 1)];
+        a1n = x1[xoff(ks + 1)];
+        bn = wh[(ks + 1) * NCH];
       }
+      side(ks);
       __builtin_amdgcn_sched_barrier(0);
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, bv, acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, bv, acc[1], 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, a0, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, a1, acc[1], 0, 0, 0);
       a0 = a0n;
       a1 = a1n;
       bv = bn;
     }
-    __syncthreads();  // every read of the input tile is done
-    // result register r of lane l: pixel 8 (r / 4) + 4 (l / 32) + r % 4 of the M tile, output channel l % 32
+  };
+  auto finish = [&](float* op, int j) {
+    at_offset(op + chan(j & 15) * HW, at[j >> 4]) = MODE == 0 || keep[j] > 0.f ? res[j] : 0.f;
+  };
+  int before = -1;
+  for (; u < nunits; before = u, u += gridDim.x) {
+    const int next = u + (int)gridDim.x < nunits ? u + gridDim.x : u;
+    const Source then = source(next);
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int p = (2 * w + mt) * 32 + 8 * (r >> 2) + 4 * kb + (r & 3);
-        float o = acc[mt][r] + bias;
-        if (MODE == 0) o = fmaxf(o, 0.f);
-        ot[n * OS + p] = o;
+      for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+    __syncthreads();  // the first half is in LDS, the second of the unit before is read
+    phase(0, [&](int ks) {
+      if (ks < ITEMS) {
+        put(1, ks, h1[ks], now);
+        h0[ks] = load(sample(next, 0), ks, then);
+      } else if (ks < ITEMS + NOUT) {
+        if (before >= 0) finish(out + corner(before), ks - ITEMS);
       }
-    __syncthreads();
-    // thread tid stores pixel tid of every channel, eight channels at a time
-    // (with relu_of, the eight activations are loaded together first)
-    float* op = out + (b * NCH * CROP + ty0 + (tid >> 4)) * CROP + tx0 + (tid & 15);
-#pragma unroll
-    for (int o0 = 0; o0 < NCH; o0 += 8) {
-      float keep[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) keep[e] = 1.f;
-      if (MODE == 1 && relu_of) {
-        const float* ap = relu_of + (op - out);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) keep[e] = ap[(o0 + e) * HW];
+    });
+    __syncthreads();  // the second half is in LDS, the first is read
+    phase(1, [&](int ks) {
+      if (ks < ITEMS) {
+        put(0, ks, h0[ks], then);
+        h1[ks] = load(sample(next, 1), ks, then);
+      } else if (MODE == 1 && ks < ITEMS + NOUT) {
+        const int j = ks - ITEMS;
+        keep[j] = at_offset(act + corner(u) + chan(j & 15) * HW, at[j >> 4]);
       }
+    });
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float o_v = ot[(o0 + e) * OS + tid];
-        op[(o0 + e) * HW] = keep[e] > 0.f ? o_v : 0.f;
-      }
+    for (int j = 0; j < NOUT; ++j) {
+      const float o = acc[j >> 4][j & 15] + bias[j & 15];
+      res[j] = MODE == 0 ? fmaxf(o, 0.f) : o;
     }
+    now = then;
   }
+#pragma unroll
+  for (int j = 0; j < NOUT; ++j) finish(out + corner(before), j);
 }
 
 // Weight and bias gradients of a conv layer as a GEMM on the matrix cores:
@@ -946,28 +1002,36 @@ __global__ __launch_bounds__(256) void k_wgrad1(const _Float16* __restrict__ x, 
 // (v_mfma_f32_16x16x4f32): [32 outputs] x
 // [288 k columns] is 2 x 18 tiles, nine per wave, so the four waves of a
 // workgroup (one per SIMD) carry equal work and two workgroups share a CU.
-// Step s takes pixels 4 s .. 4 s + 3 of the unit; every operand read is a
+// Step s takes pixels 4 s .. 4 s + 3; every operand read is a
 // constant offset from a per-lane base, and the operands of step s + 1 are
-// read before the MFMAs of step s.  The bias gradient as eight fixed
+// read before the MFMAs of step s.  Bound by the matrix cores if nothing else
+// takes their time, so a unit is two halves of eight rows, each with an LDS
+// buffer of its own: the steps of one half carry the other's values from registers
+// to LDS and the loads of the half after that (a gradient of 256 samples 1759 ->
+// 1706 us).  The bias gradient as eight fixed
 // partial sums per channel (pixels t / 32, t / 32 + 8, ... of channel
 // t % 32 for thread t), added in order.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256, 2) void k_wgrad32(const float* __restrict__ x, const float* __restrict__ dz,
                                                     int nunits, float* __restrict__ part_w,
                                                     float* __restrict__ part_b) {
-  constexpr int NK = NCH * 9, DS = 257, XC = 18 * 19, NTW = 9, NS = 64;
-  __shared__ float xt[NCH * XC];
-  __shared__ float dzt[NCH * DS];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kk = lane >> 4;
+  // row and channel strides that put the rows, taps and channels of an operand read on distinct banks
+  constexpr int NK = NCH * 9, RS = 18, XC = 184, DS = 132, NTW = 9, NS = 32;
+  // wave w carries channels 8 w .. of a half: three runs of 64 of the 180 input pixels, two of dZ's 128
+  constexpr int CW = NCH / 4, NX = 3 * CW, ITEMS = 5 * CW;
+  __shared__ float xt[2][NCH * XC];
+  __shared__ float dzt[2][NCH * DS];
+  const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, kk = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int mt = w & 1, nt0 = NTW * (w >> 1);
   // A (16 x 4): lane l holds dZ[pixel 4 s + l / 16][output 16 mt + l % 16];
   // B (4 x 16): lane l holds X[pixel 4 s + l / 16][k column 16 nt + l % 16]
-  const float* ap = dzt + (16 * mt + i16) * DS + kk;
+  const int ab = (16 * mt + i16) * DS + kk, zb = tid % NCH * DS + tid / NCH;
   int xb[NTW];
 #pragma unroll
   for (int j = 0; j < NTW; ++j) {
     const int kcol = 16 * (nt0 + j) + i16, c = kcol / 9, tap = kcol % 9;
-    xb[j] = c * XC + (tap / 3) * 19 + tap % 3 + kk;
+    xb[j] = c * XC + (tap / 3) * RS + tap % 3 + kk;
   }
   f32x4 acc[NTW];
 #pragma unroll
@@ -975,67 +1039,61 @@ __global__ __launch_bounds__(256, 2) void k_wgrad32(const float* __restrict__ x,
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[j][r] = 0.f;
   float accb = 0.f;
-  for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
-    const int ty0 = ((u & 15) >> 2) * 16, tx0 = (u & 3) * 16;
-    const float* xp = x + (long)(u >> 4) * (NCH * HW);
-    const float* zp = dz + (long)(u >> 4) * (NCH * HW);
-    // The input tile (pixel tid of every channel; then the 68 x 32 items of
-    // pixels 256 .. 323) and dZ (pixel tid of every channel), each batch of
-    // loads issued (clamped address, zeroed when stored) before its LDS
-    // writes; offsets are a per-lane value plus a constant per channel.
-    __syncthreads();  // the previous unit's reads are done
-    {
-      const int r0 = tid / 18, c0 = tid % 18, y = ty0 + r0 - 1, xx = tx0 + c0 - 1;
-      const bool in0 = y >= 0 && y < CROP && xx >= 0 && xx < CROP;
-      const float* p0 = xp + min(max(y, 0), CROP - 1) * CROP + min(max(xx, 0), CROP - 1);
-      float v[NCH];
+
+  // byte offsets in the image of a half's three runs (clamped), and whether they
+  // are inside; a value outside is zeroed on its way to LDS
+  struct Source {
+    uint32_t x[3];
+    bool in[3];
+  };
+  auto source = [&](int u, int half) {
+    const int y0 = ((u & 15) >> 2) * 16 + 8 * half - 1, x0 = (u & 3) * 16 - 1;
+    Source q;
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) v[c] = p0[c * HW];
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) xt[c * XC + r0 * 19 + c0] = in0 ? v[c] : 0.f;
+    for (int i = 0; i < 3; ++i) {
+      const int p = 64 * i + lane, yy = y0 + p / 18, xx = x0 + p % 18;
+      q.in[i] = yy >= 0 && yy < CROP && xx >= 0 && xx < CROP;
+      q.x[i] = 4 * (min(max(yy, 0), CROP - 1) * CROP + min(max(xx, 0), CROP - 1));
     }
-    {
-      constexpr int N1 = NCH * 68, P1 = (N1 + 255) / 256;
-      float v[P1];
-      uint32_t m = 0;
+    return q;
+  };
+  const uint32_t oz = 4 * ((lane >> 4) * CROP + (lane & 15));
+  auto load = [&](int u, int half, int i, const Source& q) -> float {
+    const long sample = ((long)(u >> 4) * NCH + CW * w + i % CW) * HW;
+    if (i < NX) return at_offset(x + sample, q.x[i / CW]);
+    const int row = ((u & 15) >> 2) * 16 + 8 * half + 4 * ((i - NX) / CW);
+    return at_offset(dz + sample + row * CROP + (u & 3) * 16, oz);
+  };
+  float* px = xt[0] + CW * w * XC + lane;
+  float* pz = dzt[0] + CW * w * DS + lane;
+  auto put = [&](int half, int i, float v, const Source& q) {
+    if (i < 2 * CW)
+      px[half * NCH * XC + i % CW * XC + 64 * (i / CW)] = q.in[i / CW] ? v : 0.f;
+    else if (i < NX) {
+      if (lane < 180 - 128) px[half * NCH * XC + i % CW * XC + 128] = q.in[2] ? v : 0.f;
+    } else
+      pz[half * NCH * DS + i % CW * DS + 64 * ((i - NX) / CW)] = v;
+  };
+  auto phase = [&](int half, auto&& side) {
+    const float *xh = xt[half], *zh = dzt[half];
+    auto off = [](int st) { return ((4 * st) >> 4) * RS + ((4 * st) & 15); };
+    float a = zh[ab], bv[NTW], zv = 0.f;
 #pragma unroll
-      for (int k = 0; k < P1; ++k) {
-        const int j = min(tid + 256 * k, N1 - 1), c = j / 68, pp = 256 + j % 68;
-        const int y = ty0 + pp / 18 - 1, xx = tx0 + pp % 18 - 1;
-        m |= (uint32_t)(y >= 0 && y < CROP && xx >= 0 && xx < CROP) << k;
-        v[k] = xp[(c * CROP + min(max(y, 0), CROP - 1)) * CROP + min(max(xx, 0), CROP - 1)];
-      }
-#pragma unroll
-      for (int k = 0; k < P1; ++k) {
-        const int j = tid + 256 * k, c = j / 68, pp = 256 + j % 68;
-        if (j < N1) xt[c * XC + (pp / 18) * 19 + pp % 18] = (m >> k) & 1 ? v[k] : 0.f;
-      }
-    }
-    {
-      const float* pz = zp + (ty0 + (tid >> 4)) * CROP + tx0 + (tid & 15);
-      float v[NCH];
-#pragma unroll
-      for (int o = 0; o < NCH; ++o) v[o] = pz[o * HW];
-#pragma unroll
-      for (int o = 0; o < NCH; ++o) dzt[o * DS + tid] = v[o];
-    }
-    __syncthreads();
-    // bias: thread t sums pixels t / 32, t / 32 + 8, ... of channel t % 32
-    for (int pp = tid / NCH; pp < 256; pp += 256 / NCH) accb += dzt[(tid % NCH) * DS + pp];
-    auto boff = [](int st) { return ((4 * st) >> 4) * 19 + ((4 * st) & 15); };
-    float a = ap[0], bv[NTW];
-#pragma unroll
-    for (int j = 0; j < NTW; ++j) bv[j] = xt[xb[j] + boff(0)];
+    for (int j = 0; j < NTW; ++j) bv[j] = xh[xb[j]];
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
       float an = 0.f, bn[NTW];
 #pragma unroll
       for (int j = 0; j < NTW; ++j) bn[j] = 0.f;
+      if (st > 0 && st <= NS / 2) accb += zv;
+      if (st < NS / 2) zv = zh[zb + 256 / NCH * st];
       if (st + 1 < NS) {
-        an = ap[4 * (st + 1)];
+        an = zh[ab + 4 * (st + 1)];
 #pragma unroll
-        for (int j = 0; j < NTW; ++j) bn[j] = xt[xb[j] + boff(st + 1)];
+        for (int j = 0; j < NTW; ++j) bn[j] = xh[xb[j] + off(st + 1)];
       }
+      side(st);
+      if (st + NS < ITEMS) side(st + NS);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int j = 0; j < NTW; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[j], acc[j], 0, 0, 0);
@@ -1043,6 +1101,36 @@ __global__ __launch_bounds__(256, 2) void k_wgrad32(const float* __restrict__ x,
 #pragma unroll
       for (int j = 0; j < NTW; ++j) bv[j] = bn[j];
     }
+  };
+  int u = blockIdx.x;
+  float held[ITEMS];  // the half after the one in LDS
+  Source of_held;
+  if (u < nunits) {
+    of_held = source(u, 0);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) held[i] = load(u, 0, i, of_held);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) put(0, i, held[i], of_held);
+    of_held = source(u, 1);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) held[i] = load(u, 1, i, of_held);
+  }
+  for (; u < nunits; u += gridDim.x) {
+    const int next = u + (int)gridDim.x < nunits ? u + gridDim.x : u;
+    Source q = source(next, 0);
+    __syncthreads();  // half 0 is in LDS, half 1 of the unit before is read
+    phase(0, [&](int i) {
+      put(1, i, held[i], of_held);
+      held[i] = load(next, 0, i, q);
+    });
+    of_held = q;
+    q = source(next, 1);
+    __syncthreads();  // half 1 is in LDS, half 0 is read
+    phase(1, [&](int i) {
+      put(0, i, held[i], of_held);
+      held[i] = load(next, 1, i, q);
+    });
+    of_held = q;
   }
   // D of lane l: row 4 (l / 16) + r = output channel 16 mt + 4 kk + r, column l % 16 = k column 16 nt + i16
 #pragma unroll
@@ -1051,11 +1139,11 @@ __global__ __launch_bounds__(256, 2) void k_wgrad32(const float* __restrict__ x,
     for (int r = 0; r < 4; ++r)
       part_w[((long)blockIdx.x * NCH + 16 * mt + 4 * kk + r) * NK + 16 * (nt0 + j) + i16] = acc[j][r];
   __syncthreads();
-  dzt[tid] = accb;  // the 256 partial bias sums, [part][channel]
+  dzt[0][tid] = accb;  // the 256 partial bias sums, [part][channel]
   __syncthreads();
   if (tid < NCH) {
     float sb = 0.f;
-    for (int q = 0; q < 256 / NCH; ++q) sb += dzt[q * NCH + tid];
+    for (int q = 0; q < 256 / NCH; ++q) sb += dzt[0][q * NCH + tid];
     part_b[blockIdx.x * NCH + tid] = sb;
   }
 }
