@@ -222,19 +222,11 @@ __global__ __launch_bounds__(256) void k_af_spec(const uint8_t* __restrict__ hol
 }
 
 // Sharpness of the reconstruction for CPB candidates per block.  Transfer
-// functions: from htab [nc][SUB][SUB] (candidates shared by every hologram),
-// or, with RANGES, candidate c of hologram n at
-// z = zlo[n] + (zhi[n] - zlo[n]) c / (nc - 1), H = exp(-i z kz) with
-// kz = 2 pi sqrt(1/lambda^2 - |f|^2) from the FP64 table kz (negative:
-// evanescent, H = 0).  The candidates of a block are equally spaced, so H
-// of the first one and the step factor exp(-i dz kz) are formed once per
-// pixel (phase reduced modulo 2 pi in FP64, sine and cosine of the reduced
-// angle in FP32) and H advances by one complex product per candidate.
-template <int CPB, bool RANGES>
+// functions from htab [nc][SUB][SUB], candidates shared by every hologram.
+template <int CPB>
 __global__ __launch_bounds__(256) void k_af_scan(const float2* __restrict__ sub, const float2* __restrict__ htab,
-                                                 const double* __restrict__ kz, const float* __restrict__ zlo,
-                                                 const float* __restrict__ zhi, int nc, float* __restrict__ scores) {
-  constexpr int NT = 256, S = lds_stride(SUB), QT = SUB * SUB / NT;
+                                                 int nc, float* __restrict__ scores) {
+  constexpr int NT = 256, S = lds_stride(SUB);
   __shared__ float2 A[SUB * S];
   __shared__ float2 B[SUB * S];
   __shared__ float2 tw[tw_size(SUB) > 0 ? tw_size(SUB) : 1];
@@ -243,40 +235,11 @@ __global__ __launch_bounds__(256) void k_af_scan(const float2* __restrict__ sub,
   const long n = blockIdx.x;
   fill_twiddles<SUB>(tw, tid, NT);
   const float2* sv = sub + n * SUB * SUB;
-  // RANGES: H of this block's current candidate and the step factor at the
-  // pixels q = tid + NT j of this thread
-  float2 hcur[RANGES ? QT : 1], hstep[RANGES ? QT : 1];
-  if constexpr (RANGES) {
-    const double z0 = zlo[n], z1 = zhi[n];
-    const double dz = (z1 - z0) / (nc - 1);
-    const double zc = z0 + dz * (blockIdx.y * CPB);
-    auto unit = [](double ph) {
-      const double r = ph - 6.283185307179586 * rint(ph * 0.15915494309189535);
-      float sn, cs;
-      sincosf((float)r, &sn, &cs);
-      return make_float2(cs, sn);
-    };
-#pragma unroll
-    for (int j = 0; j < QT; ++j) {
-      const double k = kz[tid + NT * j];
-      hcur[j] = k >= 0.0 ? unit(-zc * k) : make_float2(0.f, 0.f);
-      hstep[j] = k >= 0.0 ? unit(-dz * k) : make_float2(0.f, 0.f);
-    }
-  }
   for (int cc = 0; cc < CPB; ++cc) {
     const int c = blockIdx.y * CPB + cc;
     if (c >= nc) break;
-    if constexpr (RANGES) {
-#pragma unroll
-      for (int j = 0; j < QT; ++j) {
-        const int q = tid + NT * j;
-        A[(q / SUB) * S + skew(q % SUB)] = c2::mul(sv[q], hcur[j]);
-        hcur[j] = c2::mul(hcur[j], hstep[j]);
-      }
-    } else {
-      const float2* h = htab + (long)c * SUB * SUB;
-      for (int q = tid; q < SUB * SUB; q += NT) A[(q / SUB) * S + skew(q % SUB)] = c2::mul(sv[q], h[q]);
-    }
+    const float2* h = htab + (long)c * SUB * SUB;
+    for (int q = tid; q < SUB * SUB; q += NT) A[(q / SUB) * S + skew(q % SUB)] = c2::mul(sv[q], h[q]);
     __syncthreads();
     fft_lds<SUB, SUB, NT, +1>(A, tw, tid);  // rows
     for (int q = tid; q < SUB * SUB; q += NT) {
@@ -305,6 +268,139 @@ __global__ __launch_bounds__(256) void k_af_scan(const float2* __restrict__ sub,
       scores[n * nc + c] = (float)(s2 / ((SUB - 1) * (SUB - 1)) - m * m);
     }
     __syncthreads();
+  }
+}
+
+// The same for candidates of a hologram's own range, candidate c of hologram n at
+// z = zlo[n] + (zhi[n] - zlo[n]) c / (nc - 1), H = exp(-i z kz) with
+// kz = 2 pi sqrt(1/lambda^2 - |f|^2) from the FP64 table kz (negative:
+// evanescent, H = 0).  The candidates of a block are equally spaced, so H
+// of the first one and the step factor exp(-i dz kz) are formed once per
+// pixel (phase reduced modulo 2 pi in FP64, sine and cosine of the reduced
+// angle in FP32) and H advances by one complex product per candidate.
+//
+// Bound by latency: a block is a chain of transforms.  Wave w transforms rows
+// 16 w .. and then columns 16 w .. by itself, the products with H being the first
+// pass's operands; the one LDS tile is shared only to turn the rows into columns
+// and for a column's neighbour in the differences, so a candidate takes four
+// barriers in place of some thirty, a magnitude is formed once, and four
+// workgroups share a CU (16 candidates of 1000 holograms 183 -> 108 us; of 128,
+// one workgroup to a CU, still 52).  The shared candidates above keep their kernel:
+// this scheme takes a full scan of 1024 holograms to 1.65 ms, and a scan seeded by
+// the network (0.81 ms), which the tests hold to 2.5 times less, has to get
+// faster first.
+template <int CPB>
+__global__ __launch_bounds__(256, 4) void k_af_scan_ranges(const float2* __restrict__ sub, const double* __restrict__ kz,
+                                                           const float* __restrict__ zlo, const float* __restrict__ zhi,
+                                                           int nc, float* __restrict__ scores) {
+  constexpr int NT = 256, NW = NT / 64, RW = SUB / NW, S = lds_stride(SUB), U = fft_first_slots<SUB, RW, 64>(),
+                R = SUB * RW / 64 / U;
+  static_assert(U == fft_last_slots<SUB, RW, 64>() && RW * SUB == 64 * U * R, "every lane has the same butterflies");
+  __shared__ float2 A[SUB * S];  // rows, then columns, then the columns' magnitudes (FP32, at the columns' starts)
+  __shared__ float2 tw[tw_size(SUB) > 0 ? tw_size(SUB) : 1];
+  __shared__ double red[2][NW][2];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const long n = blockIdx.x;
+  fill_twiddles<SUB>(tw, tid, NT);
+  const float2* sv = sub + n * SUB * SUB;
+  auto pixel = [&](int u, int r) {  // element r of butterfly u of the row transforms' first pass
+    int b, i;
+    fft_first_index<SUB, RW, 64>(lane, u, r, &b, &i);
+    return (w * RW + b) * SUB + i;
+  };
+  // H of this block's current candidate and the step factor at this thread's pixels
+  float2 hcur[U * R], hstep[U * R];
+  {
+    const double z0 = zlo[n], z1 = zhi[n];
+    const double dz = (z1 - z0) / (nc - 1);
+    const double zc = z0 + dz * (blockIdx.y * CPB);
+    auto unit = [](double ph) {
+      const double r = ph - 6.283185307179586 * rint(ph * 0.15915494309189535);
+      float sn, cs;
+      sincosf((float)r, &sn, &cs);
+      return make_float2(cs, sn);
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double k = kz[pixel(u, r)];
+        hcur[u * R + r] = k >= 0.0 ? unit(-zc * k) : make_float2(0.f, 0.f);
+        hstep[u * R + r] = k >= 0.0 ? unit(-dz * k) : make_float2(0.f, 0.f);
+      }
+  }
+  __syncthreads();
+  float2* mine = A + w * RW * S;
+  for (int cc = 0; cc < CPB; ++cc) {
+    const int c = blockIdx.y * CPB + cc;
+    if (c >= nc) break;
+    float2 v[U][R];
+    fft_lds_io<SUB, RW, 64, +1>(
+        mine, tw, lane,
+        [&](int u, int r, int, int) {
+          const float2 p = c2::mul(sv[pixel(u, r)], hcur[u * R + r]);
+          hcur[u * R + r] = c2::mul(hcur[u * R + r], hstep[u * R + r]);
+          return p;
+        },
+        [&](int u, int r, int, int, float2 x) { v[u][r] = x; });
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        int b, i;
+        fft_last_index<SUB, RW, 64>(lane, u, r, &b, &i);
+        A[i * S + skew(w * RW + b)] = v[u][r];
+      }
+    __syncthreads();
+    constexpr float inv = 1.0f / (SUB * SUB);
+    float mag[U][R];
+    fft_lds_io<SUB, RW, 64, +1>(mine, tw, lane, nullptr, [&](int u, int r, int, int, float2 x) {
+      mag[u][r] = sqrtf(x.x * x.x + x.y * x.y) * inv;
+    });
+    tile_sync<64>();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        int b, i;
+        fft_last_index<SUB, RW, 64>(lane, u, r, &b, &i);
+        reinterpret_cast<float*>(mine + b * S)[i] = mag[u][r];
+      }
+    __syncthreads();
+    // lane = row; its columns in turn, each also the right neighbour of the one before
+    const int row = min(lane, SUB - 2), cols = w + 1 < NW ? RW : RW - 1;
+    auto at = [&](int j, int i) { return reinterpret_cast<const float*>(mine + j * S)[i]; };
+    double s1 = 0.0, s2 = 0.0;
+    float a = at(0, row);
+#pragma unroll
+    for (int j = 0; j < RW; ++j)
+      if (j < cols) {
+        const float ax = at(j + 1, row), ay = at(j, row + 1);
+        const float gx = ax - a, gy = ay - a;
+        const double g = sqrt((double)gx * gx + (double)gy * gy);
+        s1 += g;
+        s2 += g * g;
+        a = ax;
+      }
+    if (lane > SUB - 2) s1 = s2 = 0.0;
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) {
+      s1 += __shfl_xor(s1, m);
+      s2 += __shfl_xor(s2, m);
+    }
+    double(*part)[2] = red[cc & 1];
+    if (lane == 0) {
+      part[w][0] = s1;
+      part[w][1] = s2;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      s1 = (part[0][0] + part[1][0]) + (part[2][0] + part[3][0]);
+      s2 = (part[0][1] + part[1][1]) + (part[2][1] + part[3][1]);
+      const double m = s1 / ((SUB - 1) * (SUB - 1));
+      scores[n * nc + c] = (float)(s2 / ((SUB - 1) * (SUB - 1)) - m * m);
+    }
   }
 }
 
@@ -1634,9 +1730,8 @@ hv_status hv_af_scan(hv_ctx* ctx, const uint8_t* holo, int n, int ny, int nx, do
   if ((s = sc.ensure((size_t)n * n_candidates * 4, &ctx->held))) return s;
   if ((s = af_spectrum(holo, n, nullptr, false, (float2*)sb.ptr, st))) return s;
   constexpr int CPB = 8;
-  hipLaunchKernelGGL((k_af_scan<CPB, false>), dim3(n, (n_candidates + CPB - 1) / CPB), dim3(256), 0, st,
-                     (const float2*)sb.ptr, (const float2*)tab.ptr, (const double*)nullptr, (const float*)nullptr,
-                     (const float*)nullptr, n_candidates, (float*)sc.ptr);
+  hipLaunchKernelGGL(k_af_scan<CPB>, dim3(n, (n_candidates + CPB - 1) / CPB), dim3(256), 0, st,
+                     (const float2*)sb.ptr, (const float2*)tab.ptr, n_candidates, (float*)sc.ptr);
   hipLaunchKernelGGL(k_af_argmax, dim3((n + 255) / 256), dim3(256), 0, st, (const float*)sc.ptr, n, n_candidates,
                      z_lo_m, z_hi_m, (float*)nullptr, (float*)nullptr, z_out, (float*)nullptr, 0);
   if (scores_out &&
@@ -1678,8 +1773,8 @@ static hv_status af_scan_ranges(hv_ctx* ctx, const float2* sub, int n, const dou
   hv_status s;
   if ((s = sc.ensure((size_t)n * nc * 4, &ctx->held))) return s;
   constexpr int CPB = 8;
-  hipLaunchKernelGGL((k_af_scan<CPB, true>), dim3(n, (nc + CPB - 1) / CPB), dim3(256), 0, st, sub, (const float2*)nullptr,
-                     kz, (const float*)zlo, (const float*)zhi, nc, (float*)sc.ptr);
+  hipLaunchKernelGGL(k_af_scan_ranges<CPB>, dim3(n, (nc + CPB - 1) / CPB), dim3(256), 0, st, sub, kz,
+                     (const float*)zlo, (const float*)zhi, nc, (float*)sc.ptr);
   hipLaunchKernelGGL(k_af_argmax, dim3((n + 255) / 256), dim3(256), 0, st, (const float*)sc.ptr, n, nc, 0.0, 0.0,
                      zlo, zhi, z_out, (float*)nullptr, refine ? 1 : 0);
   if (scores_out && hipMemcpyAsync(scores_out, sc.ptr, (size_t)n * nc * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
