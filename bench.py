@@ -44,8 +44,8 @@ def bytes_per_pxf(prec: int, nb: int) -> dict:
 
 # library sources that build the kernels and launch shapes of this workload
 # (the counter summary under profiles/ is tied to them)
-PROFILED_SOURCES = ("api.cpp", "band.hip", "fft_lds.h", "gmem.h", "hv_ctx.h", "hv_internal.h", "spatial.hip",
-                    "temporal.hip")
+PROFILED_SOURCES = ("api.cpp", "band.hip", "fft_lds.h", "field.hip", "gmem.h", "hv_ctx.h", "hv_internal.h",
+                    "reg_fft.h", "rowband.hip", "spatial.hip", "temporal.hip")
 
 
 def source_sha() -> str:
@@ -409,7 +409,7 @@ def precision_case(hv, torch, steps):
     z = 0.5 m, then (a) the STFT over windows of 64 (stride 64, bins 2..31 at
     fs 5 kHz) with its moments, (b) PCA over the same windows (components
     1..63) and (c) SSA + FFT over them (components 1..63, then the band
-    moments).  Reports frames/s per form and the GEMM kernels' useful TFLOP/s
+    moments).  Reports frames/s per form and the covariance GEMM's useful TFLOP/s
     against the matrix-core peak of their operand type; returns as well the
     GPU outputs of window 0 and the block, for the oracle check of the
     cpu_baseline leg."""
@@ -427,10 +427,9 @@ def precision_case(hv, torch, steps):
     nb = len(hv.band_bins(tp)[0])
     nwin = n // w
     npix = ny * nx
-    # useful flops per pixel and window of each GEMM (real arithmetic on
+    # useful flops per pixel and window of the GEMM (real arithmetic on
     # (re, im)-interleaved operands, K = 2W)
-    flops = {"field_coef": 2 * (2 * nb) * (2 * w), "gram": 2 * (2 * w) ** 2, "proj_energy": 2 * (2 * 63) * (2 * w),
-             "ssa_moments": 2 * (2 * nb) * (2 * w)}
+    flops = {"gram": 2 * (2 * w) ** 2}
     ctx = hv.Context(0)
     out = {"workload": f"{n} uint16 frames of {nx}x{ny} (12-bit), Fresnel z={spec.z} m, W={w} stride {w}, "
                        f"{nb} band bins, PCA components 1..63", "frames": n}
@@ -463,7 +462,7 @@ def precision_case(hv, torch, steps):
             kern[path] = kp
         ctx.set_timing(False)
         # alone on one stream: the Fresnel passes (hv_propagate of one window's
-        # frames, field written) and the DFT GEMM on that field in memory
+        # frames, field written) and the temporal DFT of that field in memory
         fld = torch.empty((w, ny, nx), dtype=torch.complex64, device="cuda")
         ctx.hv_propagate(x[:w], opt, prec, out=fld)
         torch.cuda.synchronize()
@@ -484,10 +483,9 @@ def precision_case(hv, torch, steps):
         tp_f = hv.Temporal(w, w, fs, 2 * fs / w, 31 * fs / w)
         mo = [torch.empty((1, ny, nx), dtype=torch.float32, device="cuda") for _ in range(3)]
         ms_g = _timed_passes(torch, lambda: ctx.hv_stft_moments(fld, None, tp_f, prec, out=mo), steps)
-        gemm_b = 8 * npix * w + 12 * npix
-        alone["field_coef_c64_field"] = {"avg_ms": ms_g, "field_GBs": gemm_b / (ms_g * 1e-3) / 1e9,
-                                         "frac_of_hbm_peak": gemm_b / (ms_g * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                                         "useful_TFLOPs": flops["field_coef"] * npix / (ms_g * 1e-3) / 1e12}
+        dft_b = 8 * npix * w + 12 * npix
+        alone["field_coef_c64_field"] = {"avg_ms": ms_g, "field_GBs": dft_b / (ms_g * 1e-3) / 1e9,
+                                         "frac_of_hbm_peak": dft_b / (ms_g * 1e-3) / 1e9 / HBM_PEAK_GBS}
         del fld, mo
         # PCA of one window: a single chunk, so its covariance, eigensolve and
         # projection run on one stream with nothing beside them

@@ -72,9 +72,10 @@ typedef enum {
 
 typedef enum { HV_AS = 0, HV_FRESNEL = 1 } hv_method;
 
-/* HV_PREC_FP32: FP32 FFT arithmetic, c64 intermediates, FP32 MFMA GEMMs.
- * HV_PREC_MIXED: FP32 FFT arithmetic, fp16 intermediates in memory with
- * power-of-two scaling, split fp16 (hi + lo) MFMA GEMMs with FP32
+/* HV_PREC_FP32: FP32 FFT arithmetic in space and time, c64 intermediates,
+ * FP32 MFMA GEMMs.
+ * HV_PREC_MIXED: the same FFT arithmetic, fp16 intermediates in memory with
+ * power-of-two scaling, fp16 MFMA GEMMs (coefficients split hi + lo) with FP32
  * accumulation; eigensolves stay FP64. */
 typedef enum { HV_PREC_FP32 = 0, HV_PREC_MIXED = 1 } hv_precision;
 
@@ -285,9 +286,11 @@ hv_status hv_pca(hv_ctx* ctx, const void* in, int in_t, int n, int ny, int nx, c
  * hv_stft_moments: S_k = sum_t X_f[:, t] exp(-2 pi i k t / W), with
  * M_n = sum_{k in band} f_k^n |S_k|^2 over the band of `temporal` (window
  * W = temporal->window in {16, 32, 64}, stride temporal->stride).  The
+ * components (few of them, or the few left out) are summed and put into or
+ * taken out of each pixel's samples ahead of the DFT; for other ranges the
  * projection, the back-projection and the DFT are folded into one set of
- * coefficients per window (FP64-built), so the field is read once by the
- * coefficient GEMM after the Gram GEMM.
+ * coefficients per window (FP64-built) for a GEMM.  Either way the field is
+ * read once after the Gram GEMM.
  *   in       frames (HV_U8/HV_U16 with optics) or field (HV_C64, optics NULL)
  *   m0..m2   [J][ny][nx] float32 (nullable, not all)
  *   eigvals  [J][W] float64 (nullable), offdiag [J] (nullable) as in hv_pca

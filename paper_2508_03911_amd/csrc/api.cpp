@@ -897,8 +897,8 @@ static hv_status stft_band_first(Ctx* ctx, const void* in, int in_t, int ny, int
 }
 
 // One chunk of the frames-first order: windows j0 .. j0 + g_n - 1 of the
-// call (frames from j0 * stride), spatial passes then the temporal GEMM with
-// the moment epilogue; outputs at window j0 of m0/m1/m2/spec.
+// call (frames from j0 * stride), spatial passes then the temporal transform
+// with the moment epilogue; outputs at window j0 of m0/m1/m2/spec.
 static hv_status frames_first_chunk(Ctx* ctx, const void* in, int in_t, int ny, int nx, const hv_optics& o,
                                     const FieldBand& band, int nb, int w, int stride, int j0, int g_n, bool mixed,
                                     float* m0, float* m1, float* m2, float2* spec, hipStream_t st,
@@ -1234,9 +1234,8 @@ struct EigOut {
 // the window, eigen-decomposition, projection onto a sub-basis).  Per chunk
 // of windows: the field (spatial passes), the Gram partials and their FP64
 // reduction, the FP64 Jacobi; then, for PCA (ssa == nullptr), the
-// projection energy of components comp_lo..comp_hi, and for SSA the
-// coefficients of "project onto those components and back, then the DFT of
-// the band bins" and the coefficient GEMM with the moment epilogue.
+// projection energy of components comp_lo..comp_hi, and for SSA the moments of
+// "project onto those components and back, then the DFT of the band bins".
 static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, int nx, const hv_optics* optics,
                           int w, int stride, int comp_lo, int comp_hi, bool mixed, const DftPlan* ssa,
                           const EigOut& o, hipStream_t st) {

@@ -54,7 +54,7 @@ hv_status launch_fresnel_cols(const void* in, bool half_in, void* out, bool half
 
 // ---------------------------------------------------------------- temporal kernels
 
-// Coefficient GEMM description shared by the DFT-moment and PCA kernels.
+// Coefficient GEMM description of the PCA and SSA kernels.
 // Rows of the coefficient matrix come in (real, imaginary) pairs; npair
 // pairs padded to mtiles * 16.  The B operand is the window's field as a
 // [2W x pixels] real matrix with row 2t + c = component c of frame t.

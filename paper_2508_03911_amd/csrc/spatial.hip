@@ -9,8 +9,8 @@
 //                 columns);
 //   K2 column   : column FFT, the -fx column from Hermitian symmetry,
 //                 multiply by H_z, inverse column FFT, write [t][ny][nx];
-//   K3 row inv  : inverse row FFT to the field (or fused with the temporal
-//                 GEMM elsewhere).
+//   K3 row inv  : inverse row FFT to the field (or after the temporal
+//                 transform, of the band's bins only, elsewhere).
 // Fresnel (Abstract; Sec. VI-B.2): chirp * centred DFT * chirp, the
 // centring folded into the chirps as a (-1)^(m+n) checkerboard.
 #include <hip/hip_runtime.h>
