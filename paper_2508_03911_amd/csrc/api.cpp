@@ -563,6 +563,17 @@ static hv_status run(Ctx* c, const char* name, hipStream_t st, const FixedWs* fi
   return fixed ? f() : timed(c, name, st, std::forward<F>(f));
 }
 
+// Frame sides whose real rows go two to a transform and whose columns -fx come from
+// those of +fx (K1, K2) instead of complex rows and every column: a quarter fewer
+// bytes and transforms.  Heights 320 and 384 (whole moments of 2^27 pixels, us, 512
+// wide: 1045 -> 840 and 1007 -> 831; 32 frames 56 -> 48 and 61 -> 53) only in FP32:
+// fp16 storage would round the half spectrum elsewhere than the complex one.  1280
+// has room for four columns a tile and loses (256 wide: 1064 -> 1136); 800 has no
+// tile that splits over the threads.
+static bool real_packed(int ny, int nx, bool mixed) {
+  return pow2_in(nx, 64, 1024) && (pow2_in(ny, 64, 1024) || (!mixed && (ny == 320 || ny == 384)));
+}
+
 hv_status spatial(Ctx* c, const void* in, int in_t, int nf, int ny, int nx, const hv_optics& o, bool mixed,
                   bool want_field, float f_scale, hipStream_t st, SpatialOut& out, const FixedWs* fixed = nullptr) {
   const size_t cplx = mixed ? 4 : 8;
@@ -577,7 +588,7 @@ hv_status spatial(Ctx* c, const void* in, int in_t, int nf, int ny, int nx, cons
     if (!p) return s;
     void *zb = nullptr, *tb = nullptr;
     if ((s = ws_get(c, st, 1, (size_t)nf * frame * cplx, fixed, &zb))) return s;
-    if (in_t == HV_C64 || !pow2_in(nx, 64, 1024) || !pow2_in(ny, 64, 1024)) {
+    if (in_t == HV_C64 || !real_packed(ny, nx, mixed)) {
       // complex rows (no real-input packing), full columns: any supported side
       if ((s = ws_get(c, st, 0, (size_t)nf * frame * cplx, fixed, &tb))) return s;
       if ((s = run(c, "rows_c2c", st, fixed, [&] { return launch_rows_c2c(in, in_t, tb, mixed, nullptr, nullptr, -1, nf, ny, nx, s1, st); }))) return s;

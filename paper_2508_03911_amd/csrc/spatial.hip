@@ -233,14 +233,21 @@ __global__ __launch_bounds__(NT) void k_col_as(const TIO* __restrict__ in, TIO* 
   const int half = nx / 2;
   fill_twiddles<NY>(tw, tid, NT);
   // element u of this thread in the BC x NY tile: column s = st + row_i(u),
-  // frequency fy = yt + col_i(u)
+  // frequency fy = yt + col_i(u); of a mixed-radix NY element tid + u NT
+  constexpr bool P2 = skewed(NY);
   using TS = TileSplit<NY, NT>;
   const int st = TS::row_thr(tid), yt = TS::col_thr(tid);
-  const uint32_t off_h = (uint32_t)(st * NY + yt) * 8u;
+  const uint32_t off_h = (uint32_t)(P2 ? st * NY + yt : tid) * 8u;
+  auto h_at = [](int u) { return P2 ? TS::row_i(u) * NY + TS::col_i(u) : u * NT; };
   const TIO* src = in + (t * half + f0) * (long)NY;
   const float2* hpos = hs + (long)f0 * NY;
   const float2* hneg = hs + ((long)half + f0) * NY;
-  float2* lds = buf + st * S + skew(yt);
+  float2* lds = buf + st * S + place<NY>(yt);
+  auto slot = [&](int u, int first) -> float2& {  // element u in LDS, sequences from `first`
+    if constexpr (P2) return lds[(first + TS::row_i(u)) * S + skew(TS::col_i(u))];
+    const int e = tid + u * NT;
+    return buf[(first + e / NY) * S + e % NY];
+  };
   // The forward column FFT's first pass reads straight from registers:
   // element (u, r) of this thread is column b_u at frequency i_u + r * SP
   // (16 lanes take 16 consecutive values of one column), so the input is
@@ -264,8 +271,8 @@ __global__ __launch_bounds__(NT) void k_col_as(const TIO* __restrict__ in, TIO* 
   float2 ha[U], hb[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    ha[u] = ld_off(hpos + TS::row_i(u) * NY + TS::col_i(u), off_h);
-    hb[u] = ld_off(hneg + TS::row_i(u) * NY + TS::col_i(u), off_h);
+    ha[u] = ld_off(hpos + h_at(u), off_h);
+    hb[u] = ld_off(hneg + h_at(u), off_h);
   }
   fft_lds_io<NY, BC, NT, -1>(buf, tw, tid, [&](int u, int r, int, int) { return load_c(&v0[u][r]); }, nullptr);
   // Sequences BC..2BC-1 are free until the inverse transform: the -fx
@@ -274,10 +281,10 @@ __global__ __launch_bounds__(NT) void k_col_as(const TIO* __restrict__ in, TIO* 
   float2 va[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int s = st + TS::row_i(u), fy = yt + TS::col_i(u);
+    const int e = tid + u * NT, s = P2 ? st + TS::row_i(u) : e / NY, fy = P2 ? yt + TS::col_i(u) : e % NY;
     const float2* col = buf + s * S;
-    float2 z1 = col[skew(fy)];
-    float2 z2 = c2::conj(col[skew((NY - fy) & (NY - 1))]);
+    float2 z1 = col[place<NY>(fy)];
+    float2 z2 = c2::conj(col[place<NY>(P2 ? (NY - fy) & (NY - 1) : fy ? NY - fy : 0)]);
     float2 a, b;
     if (f0 + s == 0) {
       a = c2::scale(c2::add(z1, z2), 0.5f);
@@ -288,11 +295,11 @@ __global__ __launch_bounds__(NT) void k_col_as(const TIO* __restrict__ in, TIO* 
       b = z2;
     }
     va[u] = c2::mul(a, ha[u]);
-    lds[(BC + TS::row_i(u)) * S + skew(TS::col_i(u))] = c2::mul(b, hb[u]);
+    slot(u, BC) = c2::mul(b, hb[u]);
   }
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < U; ++u) lds[TS::row_i(u) * S + skew(TS::col_i(u))] = va[u];
+  for (int u = 0; u < U; ++u) slot(u, 0) = va[u];
   __syncthreads();
   fft_lds<NY, 2 * BC, NT, +1>(buf, tw, tid);
   // output row y = yo + k * RPK, sequence i: +fx column f0 + i for i < BC,
@@ -304,11 +311,11 @@ __global__ __launch_bounds__(NT) void k_col_as(const TIO* __restrict__ in, TIO* 
   if (i >= BC) c = f0 + i - BC == 0 ? half : nx - (f0 + i - BC);
   const uint32_t off_out = (uint32_t)(yo * nx + c) * (uint32_t)sizeof(TIO);
   TIO* dst = out + t * (long)NY * nx;
-  const float2* row = buf + i * S + skew(yo);
+  const float2* row = buf + i * S + place<NY>(yo);
 #pragma unroll 4
   for (int k = 0; k < NY / RPK; ++k) {
     TIO v;
-    store_c(&v, row[skew(k * RPK)]);
+    store_c(&v, row[place<NY>(k * RPK)]);
     st_off(dst + (long)k * RPK * nx, off_out, v);
   }
 }
@@ -563,9 +570,11 @@ void go_r2c(const void* in, void* out, int n, int ny, float scale, hipStream_t s
 // frames does not enter: another tile's last bits differ, and a frame's bits must
 // not depend on its company.  fp16 storage, which would carry a last-bit
 // difference on, keeps 32, and a frame 64 high has no gain (512 wide: 635 us against 666).
+// Eight of the heights 320 and 384, whose columns have to split over the threads.
 template <int NY, typename TIO>
 void go_col_as(const void* in, void* out, const float2* hs, int n, int nx, hipStream_t st) {
-  constexpr int BC = NY == 128 && sizeof(TIO) == 8 ? 16 : cap32(4096 / NY);  // divides nx/2 >= 32
+  constexpr int BC =  // divides nx/2 >= 32
+      !skewed(NY) ? 8 : NY == 128 && sizeof(TIO) == 8 ? 16 : cap32(4096 / NY);
   hipLaunchKernelGGL((k_col_as<NY, BC, TIO>), dim3((nx / 2) / BC * n), dim3(NT), 0, st, (const TIO*)in,
                      (TIO*)out, hs, nx, n % 8 == 0);
 }
@@ -672,6 +681,8 @@ hv_status launch_col_as(const void* in, void* out, bool half_io, const float2* h
                         hipStream_t st) {
   if (n <= 0) return HV_OK;
   if (half_io) { HV_SWITCH_N(ny, (go_col_as<N_, hv_h2>(in, out, hs, n, nx, st))); }
+  else if (ny == 320) go_col_as<320, float2>(in, out, hs, n, nx, st);
+  else if (ny == 384) go_col_as<384, float2>(in, out, hs, n, nx, st);
   else { HV_SWITCH_N(ny, (go_col_as<N_, float2>(in, out, hs, n, nx, st))); }
   return launched("col_as");
 }
