@@ -1234,6 +1234,8 @@ hv_status hv_stft_volume(hv_ctx* ctx, const void* in, int in_t, int n, int ny, i
 // Sweep limit of the FP64 Jacobi eigensolver (cyclic sweeps converge
 // quadratically; W = 64 windows of camera data take well under 20).
 static constexpr int kJacobiSweeps = 40;
+// The most that one stream's rotation log takes, unless one window needs more.
+static constexpr size_t kLogBytes = (size_t)1 << 30;
 
 // Outputs of the eigen-decomposition paths (each nullable except as noted).
 struct EigOut {
@@ -1266,9 +1268,11 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
   }
   int gw = chunk >= w ? (chunk - w) / stride + 1 : 1;
   if (gw < 1) gw = 1;
+  if (gw > nwin_total) gw = nwin_total;
   // per-window scratch of one chunk, one set per stream
   struct Scratch {
     void *part, *cv, *ev, *vec, *a32, *a16h, *a16l, *log, *vec32;
+    int log_windows;
   };
   const size_t M = 2 * (size_t)w;
   // Few components left out (or, PCA, few kept): one lane per pixel takes them
@@ -1279,18 +1283,30 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
                           : field_energy_fits(half_field, w, comp_lo, comp_hi);
   auto scratch = [&](hipStream_t cs, Scratch* x) -> hv_status {
     const size_t coefs = direct ? 0 : (size_t)gw * mtiles * w * 64;
-    const size_t bytes[9] = {(size_t)gw * nblk * M * M * 4, (size_t)gw * w * w * 16, (size_t)gw * w * 8,
-                             (size_t)gw * w * w * 16, coefs * 4, coefs * 2, coefs * 2,
-                             jacobi_log_bytes(gw, w, kJacobiSweeps), (size_t)gw * w * w * 8};
-    void** dst[9] = {&x->part, &x->cv, &x->ev, &x->vec, &x->a32, &x->a16h, &x->a16l, &x->log, &x->vec32};
-    const int slot[9] = {10, 11, 12, 13, 14, 15, 16, 18, 19};
-    for (int i = 0; i < 9; ++i) {
+    const size_t bytes[8] = {(size_t)gw * nblk * M * M * 4, (size_t)gw * w * w * 16, (size_t)gw * w * 8,
+                             (size_t)gw * w * w * 16, coefs * 4, coefs * 2, coefs * 2, (size_t)gw * w * w * 8};
+    void** dst[8] = {&x->part, &x->cv, &x->ev, &x->vec, &x->a32, &x->a16h, &x->a16l, &x->vec32};
+    const int slot[8] = {10, 11, 12, 13, 14, 15, 16, 19};
+    hv_status e;
+    for (int i = 0; i < 8; ++i) {
       DevBuf& b = ctx->work(cs, slot[i]);
-      hv_status e = b.ensure(bytes[i], &ctx->held);
-      if (e) return e;
+      if ((e = b.ensure(bytes[i], &ctx->held))) return e;
       *dst[i] = b.ptr;
     }
-    return HV_OK;
+    // The rotation log keeps room for every sweep up to the limit (1.9 MB a window
+    // of 64 frames), so small frames with a short stride, whose chunks hold up to
+    // two thousand windows, take kLogBytes of windows at a time (554 of 64
+    // frames; two fit a CU), and fewer where the device has not that room.
+    // 2048 frames of 64^2 at W = 64, stride 1, us and MiB held: 7,150 and 4,259
+    // with a log for all 1,985 windows, 7,630 and 1,618 with 1 GiB, 8,861 and
+    // 1,107 with 512 MiB.
+    DevBuf& lg = ctx->work(cs, 18);
+    x->log_windows = (int)std::min<size_t>(gw, std::max<size_t>(1, kLogBytes / jacobi_log_bytes(1, w, kJacobiSweeps)));
+    while ((e = lg.ensure(jacobi_log_bytes(x->log_windows, w, kJacobiSweeps), &ctx->held)) == HV_ERR_NOMEM &&
+           x->log_windows > 1)
+      x->log_windows = (x->log_windows + 1) / 2;
+    x->log = lg.ptr;
+    return e;
   };
   const float* wts = nullptr;
   if (ssa) {
@@ -1348,7 +1364,7 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
         return s;
       if ((s = timed(ctx, "jacobi", st, [&] {
              return launch_jacobi((const double*)x.cv, g_n, w, (double*)x.ev, (double*)x.vec,
-                                  o.offdiag ? o.offdiag + j0 : nullptr, kJacobiSweeps, x.log,
+                                  o.offdiag ? o.offdiag + j0 : nullptr, kJacobiSweeps, x.log, x.log_windows,
                                   (float2*)x.vec32, st);
            })))
         return s;

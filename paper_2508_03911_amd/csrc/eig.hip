@@ -376,20 +376,28 @@ size_t jacobi_log_bytes(int nwin, int window, int max_sweeps) {
 }
 
 hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, double* evecs, double* offdiag,
-                        int max_sweeps, void* log_ws, float2* vec32, hipStream_t st) {
+                        int max_sweeps, void* log_ws, int log_windows, float2* vec32, hipStream_t st) {
   if (nwin <= 0) return HV_OK;
-  const size_t n = log_entries(nwin, window, max_sweeps);
+  if (log_windows < 1) return fail(HV_ERR_ARG, "the rotation log holds no window");
+  const size_t n = log_entries(log_windows, window, max_sweeps);
   JacobiLog log;
   log.s = (dc*)log_ws;
   log.c = (double*)(log.s + n);
   log.steps = (int*)(log.c + n);
-  log.rank = log.steps + nwin;
+  log.rank = log.steps + log_windows;
   log.max_sweeps = max_sweeps;
-  switch (window) {
-    case 16: go_jacobi<16>(cov, nwin, evals, evecs, offdiag, log, vec32, st); break;
-    case 32: go_jacobi<32>(cov, nwin, evals, evecs, offdiag, log, vec32, st); break;
-    case 64: go_jacobi<64>(cov, nwin, evals, evecs, offdiag, log, vec32, st); break;
-    default: return fail(HV_ERR_SHAPE, "PCA window %d not supported", window);
+  const size_t w = (size_t)window;
+  for (int j = 0; j < nwin; j += log_windows) {
+    const int g = nwin - j < log_windows ? nwin - j : log_windows;
+    const double* c = cov + j * w * w * 2;
+    double *ev = evals + j * w, *vec = evecs + j * w * w * 2, *off = offdiag ? offdiag + j : nullptr;
+    float2* v32 = vec32 + j * w * w;
+    switch (window) {
+      case 16: go_jacobi<16>(c, g, ev, vec, off, log, v32, st); break;
+      case 32: go_jacobi<32>(c, g, ev, vec, off, log, v32, st); break;
+      case 64: go_jacobi<64>(c, g, ev, vec, off, log, v32, st); break;
+      default: return fail(HV_ERR_SHAPE, "PCA window %d not supported", window);
+    }
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(HV_ERR_DEVICE, "jacobi launch failed: %s", hipGetErrorString(e));

@@ -121,11 +121,12 @@ hv_status launch_gram_reduce(const float* part, int nwin, int nblk, int window, 
 // eigenvectors (columns, complex f64 interleaved) [nwin][W][W]; offdiag
 // (nullable) [nwin] receives sqrt(off-diagonal / total squared magnitude)
 // when the window stops (converged below 1e-15, or max_sweeps reached); log_ws:
-// 16-byte aligned workspace of jacobi_log_bytes for the rotations; vec32
-// [nwin][component][W] receives the eigenvectors in single precision.
+// 16-byte aligned workspace of jacobi_log_bytes(log_windows, ..) for the
+// rotations, of as many windows at a time; vec32 [nwin][component][W] receives
+// the eigenvectors in single precision.
 size_t jacobi_log_bytes(int nwin, int window, int max_sweeps);
 hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, double* evecs, double* offdiag,
-                        int max_sweeps, void* log_ws, float2* vec32, hipStream_t st);
+                        int max_sweeps, void* log_ws, int log_windows, float2* vec32, hipStream_t st);
 // Build per-window projection coefficient fragments from eigenvectors
 // columns c1..c2 (A = [Vr^T Vi^T ; ...]) for the coefficient GEMM.
 hv_status launch_proj_coefs(const double* evecs, int nwin, int window, int c1, int c2, int mtiles,
