@@ -1282,9 +1282,10 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
   const bool direct = ssa ? field_dft_fits(half_field, w, comp_lo, comp_hi)
                           : field_energy_fits(half_field, w, comp_lo, comp_hi);
   auto scratch = [&](hipStream_t cs, Scratch* x) -> hv_status {
-    const size_t coefs = direct ? 0 : (size_t)gw * mtiles * w * 64;
+    // the FP64 vectors are read by the coefficient kernels, the FP32 ones by the others
+    const size_t coefs = direct ? 0 : (size_t)gw * mtiles * w * 64, vecs = (size_t)gw * w * w;
     const size_t bytes[8] = {(size_t)gw * nblk * M * M * 4, (size_t)gw * w * w * 16, (size_t)gw * w * 8,
-                             (size_t)gw * w * w * 16, coefs * 4, coefs * 2, coefs * 2, (size_t)gw * w * w * 8};
+                             direct ? 0 : vecs * 16, coefs * 4, coefs * 2, coefs * 2, direct ? vecs * 8 : 0};
     void** dst[8] = {&x->part, &x->cv, &x->ev, &x->vec, &x->a32, &x->a16h, &x->a16l, &x->vec32};
     const int slot[8] = {10, 11, 12, 13, 14, 15, 16, 19};
     hv_status e;
@@ -1363,9 +1364,9 @@ static hv_status eig_path(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
       if ((s = launch_gram_reduce((const float*)x.part, g_n, nblk, w, 1.0 / ((double)fs * fs), (double*)x.cv, st)))
         return s;
       if ((s = timed(ctx, "jacobi", st, [&] {
-             return launch_jacobi((const double*)x.cv, g_n, w, (double*)x.ev, (double*)x.vec,
+             return launch_jacobi((const double*)x.cv, g_n, w, (double*)x.ev, direct ? nullptr : (double*)x.vec,
                                   o.offdiag ? o.offdiag + j0 : nullptr, kJacobiSweeps, x.log, x.log_windows,
-                                  (float2*)x.vec32, st);
+                                  direct ? (float2*)x.vec32 : nullptr, st);
            })))
         return s;
       const size_t at = (size_t)j0 * frame;

@@ -348,12 +348,16 @@ __global__ __launch_bounds__(128) void k_jacobi_vectors(JacobiLog log, double* _
     }
   }
   const int* rank = log.rank + jj * W;
-  dc* dst = reinterpret_cast<dc*>(evecs) + (jj * W + row) * W;
-  dst[rank[k]] = t;
-  dst[rank[W - 1 - k]] = b;
-  float2* v = vec32 + jj * W * W + row;
-  v[rank[k] * W] = make_float2((float)t.x, (float)t.y);
-  v[rank[W - 1 - k] * W] = make_float2((float)b.x, (float)b.y);
+  if (evecs) {
+    dc* dst = reinterpret_cast<dc*>(evecs) + (jj * W + row) * W;
+    dst[rank[k]] = t;
+    dst[rank[W - 1 - k]] = b;
+  }
+  if (vec32) {
+    float2* v = vec32 + jj * W * W + row;
+    v[rank[k] * W] = make_float2((float)t.x, (float)t.y);
+    v[rank[W - 1 - k] * W] = make_float2((float)b.x, (float)b.y);
+  }
 }
 
 template <int W>
@@ -390,8 +394,8 @@ hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, 
   for (int j = 0; j < nwin; j += log_windows) {
     const int g = nwin - j < log_windows ? nwin - j : log_windows;
     const double* c = cov + j * w * w * 2;
-    double *ev = evals + j * w, *vec = evecs + j * w * w * 2, *off = offdiag ? offdiag + j : nullptr;
-    float2* v32 = vec32 + j * w * w;
+    double *ev = evals + j * w, *vec = evecs ? evecs + j * w * w * 2 : nullptr, *off = offdiag ? offdiag + j : nullptr;
+    float2* v32 = vec32 ? vec32 + j * w * w : nullptr;
     switch (window) {
       case 16: go_jacobi<16>(c, g, ev, vec, off, log, v32, st); break;
       case 32: go_jacobi<32>(c, g, ev, vec, off, log, v32, st); break;

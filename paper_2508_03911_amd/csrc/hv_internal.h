@@ -118,12 +118,12 @@ hv_status launch_gram_partials(const void* u, bool half_in, long npix, int strid
 hv_status launch_gram_reduce(const float* part, int nwin, int nblk, int window, double cscale, double* cov,
                              hipStream_t st);
 // FP64 cyclic Jacobi on each window's C: eigenvalues (descending) and
-// eigenvectors (columns, complex f64 interleaved) [nwin][W][W]; offdiag
+// eigenvectors (columns, complex f64 interleaved, nullable) [nwin][W][W]; offdiag
 // (nullable) [nwin] receives sqrt(off-diagonal / total squared magnitude)
 // when the window stops (converged below 1e-15, or max_sweeps reached); log_ws:
 // 16-byte aligned workspace of jacobi_log_bytes(log_windows, ..) for the
-// rotations, of as many windows at a time; vec32 [nwin][component][W] receives
-// the eigenvectors in single precision.
+// rotations, of as many windows at a time; vec32 (nullable)
+// [nwin][component][W] receives the eigenvectors in single precision.
 size_t jacobi_log_bytes(int nwin, int window, int max_sweeps);
 hv_status launch_jacobi(const double* cov, int nwin, int window, double* evals, double* evecs, double* offdiag,
                         int max_sweeps, void* log_ws, int log_windows, float2* vec32, hipStream_t st);

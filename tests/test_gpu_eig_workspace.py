@@ -44,3 +44,13 @@ def test_many_windows(hv, w):
         for k in ("m0", "eigvals"):
             assert torch.equal(one[k][0], r[k][j]), (j, k)
     ctx.close()
+
+
+def test_no_double_precision_vectors_where_none_are_read(hv):
+    """A range that leaves few components out reads the single-precision vectors
+    only: 40 W^2 bytes a window."""
+    n, w = 2048, 64
+    ctx = hv.Context(0)
+    ctx.hv_pca(_frames(n), hv.Optics(852e-9, 20e-6, 20e-6, -0.2, hv.HV_AS), w, 1, 1)
+    assert ctx.workspace_bytes() < 3 * n * 4096 * 8 + (1 << 30) + (n - w + 1) * 40 * w * w + (8 << 20)
+    ctx.close()
