@@ -118,7 +118,13 @@ void hv_ctx_destroy(hv_ctx* ctx);
 const char* hv_last_error(void);
 /* Bytes of device memory held by the context's plans and workspaces. */
 size_t hv_ctx_workspace_bytes(const hv_ctx* ctx);
-/* Frames per spatial chunk (workspace size knob; 0 = automatic). */
+/* Frames per spatial chunk (workspace size knob; 0 = automatic).  Automatic:
+ * about 96 MiB of spectra per stream (at least 32 to 64 frames, one window at
+ * least); overlapping windows, whose chunks propagate their shared frames again,
+ * up to 2 GiB per stream; PCA and SSA up to 2 GiB of field per stream beside
+ * the spectra, and up to 1 GiB of eigensolver log.  Calls of more than one chunk
+ * use two streams.  Where the device has not the room for the larger chunks or
+ * the log, smaller ones are taken before a call fails. */
 hv_status hv_ctx_set_chunk_frames(hv_ctx* ctx, int frames);
 
 /* Order of the angular-spectrum STFT path of hv_stft_moments and

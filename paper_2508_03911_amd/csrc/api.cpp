@@ -22,6 +22,7 @@
 #include <tuple>
 #include <vector>
 
+#include "chunks.h"
 #include "hv_ctx.h"
 #include "hv_internal.h"
 
@@ -46,6 +47,12 @@ void DevBuf::release() {
   if (ptr) (void)hipFree(ptr);
   ptr = nullptr;
   bytes = 0;
+}
+void DevBuf::drop(size_t* accounted) {
+  // queued work may still use it
+  if (ptr && hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
+  if (accounted) *accounted -= bytes;
+  release();
 }
 hv_status DevBuf::ensure(size_t want, size_t* accounted) {
   if (want <= bytes) return HV_OK;
@@ -404,39 +411,7 @@ DevBuf& Ctx::work(hipStream_t s, int slot) {
 }
 
 int Ctx::chunk_frames_for(int ny, int nx, bool mixed) const {
-  if (chunk_frames > 0) return chunk_frames;
-  // about 96 MiB of intermediate spectra per chunk (half spectrum + full
-  // spectrum = 1.5 complex values per pixel), at least 64 frames: 128 frames
-  // (FP32) and 256 (fp16) at 256 x 256, the fastest measured with two
-  // streams in flight
-  const long per = (long)ny * nx * (mixed ? 4 : 8) * 3 / 2;
-  long f = (96L << 20) / per;
-  if (f < 64) f = 64;
-  if (f > 2048) f = 2048;
-  return (int)f;
-}
-
-// Windows per chunk of the STFT paths.  The W - stride frames that a chunk
-// shares with the next are propagated in both, so where windows overlap a
-// chunk holds at least 16 times as many new frames, within about 1 GiB of
-// intermediates per stream (times of the moments call, us, with chunks of the
-// size below and with these: 1024x512 W 32 stride 16 1097 -> 884, 384^2 W 64
-// stride 16 6266 -> 2213, 256^2 W 32 stride 8 1039 -> 962; fp16 916 -> 743, 2505 ->
-// 1768, 839 -> 787).  Without overlap the size of chunk_frames_for, but no
-// fewer than its 96 MiB where that is 32 frames or more (512^2 FP32, 64 -> 32
-// frames: 1711 -> 1512; smaller launches lose at larger frames).
-int Ctx::chunk_windows(int ny, int nx, bool mixed, int w, int stride, int nwin) const {
-  const long per = (long)ny * nx * (mixed ? 4 : 8) * 3 / 2;
-  long f = chunk_frames_for(ny, nx, mixed);
-  if (chunk_frames <= 0 && (96L << 20) / per >= 32) f = std::min(f, (96L << 20) / per);
-  auto windows = [&](long frames) { return frames >= w ? (frames - w) / stride + 1 : 1L; };
-  long g = windows(f);
-  if (chunk_frames <= 0 && stride < w) {
-    g = std::max(g, std::min(16L * (w - stride) / stride + 1, windows((1L << 30) / per)));
-    const long chunks = (nwin + g - 1) / g;  // of even size
-    g = (nwin + chunks - 1) / chunks;
-  }
-  return (int)std::min<long>(g, nwin);
+  return chunk_frames > 0 ? chunk_frames : hvc::auto_frames((long)ny * nx, mixed ? 4 : 8);
 }
 
 }  // namespace hvi
@@ -574,10 +549,47 @@ static bool real_packed(int ny, int nx, bool mixed) {
   return pow2_in(nx, 64, 1024) && (pow2_in(ny, 64, 1024) || (!mixed && (ny == 320 || ny == 384)));
 }
 
+// Bytes per frame of the workspaces that spatial() takes.
+struct SpatialBytes {
+  size_t slot[3];
+};
+static SpatialBytes spatial_bytes(int in_t, int ny, int nx, const hv_optics& o, bool mixed, bool want_field) {
+  const size_t full = (size_t)ny * nx * (mixed ? 4 : 8);
+  if (o.method != HV_AS) return {{full, 0, full}};
+  const bool packed = in_t != HV_C64 && real_packed(ny, nx, mixed);
+  return {{packed ? full / 2 : full, full, want_field ? full : 0}};
+}
+
+// The chunks of an STFT call of nwin windows, with the workspaces of spatial()
+// allocated for them on `st` and, where there is more than one, on the second
+// stream that `*l2` then points to (second: the call may use one).
+static hv_status stft_chunks(Ctx* c, hipStream_t st, bool second, const SpatialBytes& b, int ny, int nx, bool mixed,
+                             int w, int stride, int nwin, hvc::Chunk* chunk, Ctx::Lane2** l2) {
+  *l2 = nullptr;
+  *chunk = hvc::stft_chunk((long)ny * nx, mixed ? 4 : 8, c->chunk_frames, w, stride, nwin);
+  return hvc::with_room(*chunk, HV_ERR_NOMEM, [&](int g) -> hv_status {
+    hv_status s = HV_OK;
+    hipStream_t streams[2] = {st, nullptr};
+    int n = 1;
+    if (second && nwin > g) {
+      if (!(*l2 = c->lane2(st, &s))) return s;
+      streams[n++] = (*l2)->s;
+    }
+    const size_t nf = (size_t)(g - 1) * stride + w;
+    for (int i = 0; i < n; ++i)
+      for (int slot = 0; slot < 3; ++slot)
+        if (s == HV_OK && b.slot[slot]) s = c->work(streams[i], slot).ensure(nf * b.slot[slot], &c->held);
+    if (s == HV_ERR_NOMEM)
+      for (int i = 0; i < n; ++i)
+        for (int slot = 0; slot < 3; ++slot) c->work(streams[i], slot).drop(&c->held);
+    return s;
+  });
+}
+
 hv_status spatial(Ctx* c, const void* in, int in_t, int nf, int ny, int nx, const hv_optics& o, bool mixed,
                   bool want_field, float f_scale, hipStream_t st, SpatialOut& out, const FixedWs* fixed = nullptr) {
-  const size_t cplx = mixed ? 4 : 8;
-  const size_t frame = (size_t)ny * nx;
+  const SpatialBytes bytes = spatial_bytes(in_t, ny, nx, o, mixed, want_field);
+  auto ws = [&](int slot, void** p) { return ws_get(c, st, slot, nf * bytes.slot[slot], fixed, p); };
   const float s1 = mixed ? fp16_row_scale(in_t, ny, nx) : 1.0f;
   const bool build = fixed == nullptr;
   out.half = mixed;
@@ -587,14 +599,14 @@ hv_status spatial(Ctx* c, const void* in, int in_t, int nf, int ny, int nx, cons
     AsPlan* p = c->as_plan(ny, nx, o, &s, build);
     if (!p) return s;
     void *zb = nullptr, *tb = nullptr;
-    if ((s = ws_get(c, st, 1, (size_t)nf * frame * cplx, fixed, &zb))) return s;
+    if ((s = ws(1, &zb))) return s;
     if (in_t == HV_C64 || !real_packed(ny, nx, mixed)) {
       // complex rows (no real-input packing), full columns: any supported side
-      if ((s = ws_get(c, st, 0, (size_t)nf * frame * cplx, fixed, &tb))) return s;
+      if ((s = ws(0, &tb))) return s;
       if ((s = run(c, "rows_c2c", st, fixed, [&] { return launch_rows_c2c(in, in_t, tb, mixed, nullptr, nullptr, -1, nf, ny, nx, s1, st); }))) return s;
       if ((s = run(c, "col_full", st, fixed, [&] { return launch_col_full(tb, zb, mixed, p->ht_ptr(), nf, ny, nx, st); }))) return s;
     } else {
-      if ((s = ws_get(c, st, 0, (size_t)nf * (frame / 2) * cplx, fixed, &tb))) return s;
+      if ((s = ws(0, &tb))) return s;
       if ((s = run(c, "row_r2c", st, fixed, [&] { return launch_row_r2c(in, (hv_dtype)in_t, tb, mixed, nf, ny, nx, s1, st); }))) return s;
       if ((s = run(c, "col_as", st, fixed, [&] { return launch_col_as(tb, zb, mixed, p->hs_ptr(), nf, ny, nx, st); }))) return s;
     }
@@ -602,7 +614,7 @@ hv_status spatial(Ctx* c, const void* in, int in_t, int nf, int ny, int nx, cons
     out.z_to_field = 1.0f / (nx * s1);
     if (want_field) {
       void* fb = nullptr;
-      if ((s = ws_get(c, st, 2, (size_t)nf * frame * cplx, fixed, &fb))) return s;
+      if ((s = ws(2, &fb))) return s;
       if ((s = run(c, "row_inv", st, fixed, [&] { return launch_row_inv(zb, mixed, fb, mixed, nf, ny, nx, out.z_to_field * f_scale, st); }))) return s;
       out.f = fb;
     }
@@ -612,8 +624,8 @@ hv_status spatial(Ctx* c, const void* in, int in_t, int nf, int ny, int nx, cons
   if (!p) return s;
   const int dir = o.z_m > 0 ? -1 : +1;
   void *tb = nullptr, *fb = nullptr;
-  if ((s = ws_get(c, st, 0, (size_t)nf * frame * cplx, fixed, &tb))) return s;
-  if ((s = ws_get(c, st, 2, (size_t)nf * frame * cplx, fixed, &fb))) return s;
+  if ((s = ws(0, &tb))) return s;
+  if ((s = ws(2, &fb))) return s;
   const float2* q = (const float2*)p->tables.ptr;
   if ((s = run(c, "fresnel_rows", st, fixed, [&] { return launch_rows_c2c(in, in_t, tb, mixed, q, q + nx, dir, nf, ny, nx, s1, st); })))
     return s;
@@ -993,15 +1005,17 @@ static hv_status stft_impl(hv_ctx* ctx, const void* in, int in_t, int n, int ny,
       return stft_band_first(ctx, in, in_t, ny, nx, *optics, *dp, w, stride, nwin_total, gb, mixed, m0, m1, m2,
                              spec, st, two_lanes);
   }
-  const int gw = ctx->chunk_windows(ny, nx, mixed, w, stride, nwin_total);
   // Chunks alternate between the caller's stream and a second one (per-kernel
   // timing events, when on, bracket each launch on its own stream and so
   // time it as it runs beside the other stream's work).
+  const bool fused = optics->method == HV_AS && row_band_fits(nx, w, stride, nb, mixed);
+  hvc::Chunk chunk;
   Ctx::Lane2* l2 = nullptr;
-  if (two_lanes && nwin_total > gw) {
-    if (!(l2 = ctx->lane2(st, &s))) return s;
-    if ((s = l2->fork_from(st))) return s;
-  }
+  if ((s = stft_chunks(ctx, st, two_lanes, spatial_bytes(in_t, ny, nx, *optics, mixed, !fused), ny, nx, mixed, w,
+                       stride, nwin_total, &chunk, &l2)))
+    return s;
+  const int gw = chunk.windows;
+  if (l2 && (s = l2->fork_from(st))) return s;
   hv_status res = HV_OK;
   const hipStream_t caller = st;
   for (int j0 = 0, c = 0; j0 < nwin_total && res == HV_OK; j0 += gw, ++c) {
@@ -1119,14 +1133,12 @@ hv_status hv_stft_moments_host(hv_ctx* ctx, const void* host_in, int in_t, int n
   const bool mixed = prec == HV_PREC_MIXED;
   const int nwin_total = (n - w) / stride + 1;
   const size_t frame = (size_t)ny * nx, fbytes = frame * in_elem(in_t);
-  const int gw = ctx->chunk_windows(ny, nx, mixed, w, stride, nwin_total);
-  const int cf = (gw - 1) * stride + w;  // frames staged per chunk
   hipStream_t st = (hipStream_t)hip_stream;
   float* const host_out[3] = {host_m0, host_m1, host_m2};
   // staging per stream: raw frames in, moment images out
-  auto stage = [&](hipStream_t cs, void** in_dev, float** out_dev) -> hv_status {
+  auto stage = [&](int gw, hipStream_t cs, void** in_dev, float** out_dev) -> hv_status {
     DevBuf& bi = ctx->work(cs, 20);
-    hv_status e = bi.ensure((size_t)cf * fbytes, &ctx->held);
+    hv_status e = bi.ensure(((size_t)(gw - 1) * stride + w) * fbytes, &ctx->held);
     if (e) return e;
     *in_dev = bi.ptr;
     for (int k = 0; k < 3; ++k) {
@@ -1140,13 +1152,24 @@ hv_status hv_stft_moments_host(hv_ctx* ctx, const void* host_in, int in_t, int n
   };
   void* in_dev[2];
   float* out_dev[2][3];
-  if ((s = stage(st, &in_dev[0], out_dev[0]))) return s;
   Ctx::Lane2* l2 = nullptr;
-  if (nwin_total > gw) {
-    if (!(l2 = ctx->lane2(st, &s))) return s;
-    if ((s = stage(l2->s, &in_dev[1], out_dev[1]))) return s;
-    if ((s = l2->fork_from(st))) return s;
-  }
+  hvc::Chunk chunk = hvc::stft_chunk((long)frame, mixed ? 4 : 8, ctx->chunk_frames, w, stride, nwin_total);
+  if ((s = hvc::with_room(chunk, HV_ERR_NOMEM, [&](int g) -> hv_status {
+         hv_status e = stage(g, st, &in_dev[0], out_dev[0]);
+         if (e == HV_OK && nwin_total > g) {
+           if (!(l2 = ctx->lane2(st, &e))) return e;
+           e = stage(g, l2->s, &in_dev[1], out_dev[1]);
+         }
+         if (e == HV_ERR_NOMEM)
+           for (int slot = 20; slot < 24; ++slot) {
+             ctx->work(st, slot).drop(&ctx->held);
+             if (l2) ctx->work(l2->s, slot).drop(&ctx->held);
+           }
+         return e;
+       })))
+    return s;
+  const int gw = chunk.windows;
+  if (l2 && (s = l2->fork_from(st))) return s;
   // Each chunk is copied in, processed and copied out on its own stream;
   // with two streams one chunk's copies overlap the other chunk's kernels.
   hv_status res = HV_OK;
@@ -1201,14 +1224,15 @@ hv_status hv_stft_volume(hv_ctx* ctx, const void* in, int in_t, int n, int ny, i
     return timed(ctx, "time_fft", st, [&] {
       return launch_time_fft(in, false, (long)frame, stride, nwin_total, w, 1.f, power, st);
     });
-  const int gw = ctx->chunk_windows(ny, nx, mixed, w, stride, nwin_total);
   const float fsc = mixed ? fp16_field_scale(in_t, ny, nx) : 1.f;
   // chunks alternate between the caller's stream and a second one
+  hvc::Chunk chunk;
   Ctx::Lane2* l2 = nullptr;
-  if (nwin_total > gw) {
-    if (!(l2 = ctx->lane2(st, &s))) return s;
-    if ((s = l2->fork_from(st))) return s;
-  }
+  if ((s = stft_chunks(ctx, st, true, spatial_bytes(in_t, ny, nx, *optics, mixed, true), ny, nx, mixed, w, stride,
+                       nwin_total, &chunk, &l2)))
+    return s;
+  const int gw = chunk.windows;
+  if (l2 && (s = l2->fork_from(st))) return s;
   hv_status res = HV_OK;
   const hipStream_t caller = st;
   for (int j0 = 0, c = 0; j0 < nwin_total && res == HV_OK; j0 += gw, ++c) {

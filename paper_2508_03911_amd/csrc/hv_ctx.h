@@ -24,6 +24,7 @@ struct DevBuf {
   DevBuf& operator=(const DevBuf&) = delete;
   ~DevBuf();
   void release();
+  void drop(size_t* accounted);  // waits for the device, frees and takes the bytes off the owner's
   // Make room for `want` bytes (contents are not preserved); `accounted`
   // tracks the bytes held by the owner.
   hv_status ensure(size_t want, size_t* accounted);
@@ -133,7 +134,6 @@ struct Ctx {
   DftPlan* dft_plan(const hv_temporal& tp, hv_status* st, bool build = true);
   DevBuf& work(hipStream_t s, int slot);
   int chunk_frames_for(int ny, int nx, bool mixed) const;
-  int chunk_windows(int ny, int nx, bool mixed, int w, int stride, int nwin) const;
 };
 
 // Runs f() (a kernel launch), bracketed by timing events when enabled.
