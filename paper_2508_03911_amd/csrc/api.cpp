@@ -1153,7 +1153,7 @@ hv_status hv_stft_moments_host(hv_ctx* ctx, const void* host_in, int in_t, int n
   void* in_dev[2];
   float* out_dev[2][3];
   Ctx::Lane2* l2 = nullptr;
-  hvc::Chunk chunk = hvc::stft_chunk((long)frame, mixed ? 4 : 8, ctx->chunk_frames, w, stride, nwin_total);
+  hvc::Chunk chunk = hvc::stft_chunk((long)frame, mixed ? 4 : 8, ctx->chunk_frames, w, stride, nwin_total, true);
   if ((s = hvc::with_room(chunk, HV_ERR_NOMEM, [&](int g) -> hv_status {
          hv_status e = stage(g, st, &in_dev[0], out_dev[0]);
          if (e == HV_OK && nwin_total > g) {

@@ -31,14 +31,23 @@ struct Chunk {
 // auto_frames, but no more than its 96 MiB where that is 32 frames or more (512^2
 // FP32, 64 -> 32 frames: 1711 -> 1512; smaller launches lose at larger frames).
 // set_frames: the caller's frames per chunk (0: automatic).
-inline Chunk stft_chunk(long pix, int cplx, int set_frames, int w, int stride, int nwin) {
+//
+// uploaded: frames from host memory, whose chunks are copied in and out beside the
+// kernels of others.  Their chunks keep the size without overlap where that shares a
+// quarter of its new frames or less: the copies take far longer than the kernels,
+// and those of larger chunks get in each other's way (us, median, with the size
+// without overlap and with the larger: 4096 frames of 256^2 W 32 stride 16 7,995 to
+// 8,269 and 8,375 to 10,200, 2048 of stride 8 6,167 to 6,227 and 6,930, but 512 of
+// stride 16 1,360 and 1,288; 211 of 1024x512 stride 16, a third shared, 7,086 and
+// 6,430, 1024 of 384^2 W 64 stride 16, 48 frames for 16 new ones, 13,500 and 6,830).
+inline Chunk stft_chunk(long pix, int cplx, int set_frames, int w, int stride, int nwin, bool uploaded = false) {
   const long per = pix * cplx * 3 / 2;
   long f = set_frames > 0 ? set_frames : auto_frames(pix, cplx);
   if (set_frames <= 0 && (96L << 20) / per >= 32) f = std::min(f, (96L << 20) / per);
   auto windows = [&](long frames) { return frames >= w ? (frames - w) / stride + 1 : 1L; };
   const long least = std::min<long>(windows(f), nwin);
   long g = least;
-  if (set_frames <= 0 && stride < w) {
+  if (set_frames <= 0 && stride < w && !(uploaded && 4L * (w - stride) <= least * stride)) {
     g = std::max(g, std::min(16L * (w - stride) / stride + 1, windows((1L << 30) / per)));
     const long chunks = (nwin + g - 1) / g;  // of even size
     g = (nwin + chunks - 1) / chunks;

@@ -40,6 +40,12 @@ int main() {
                 const hvc::Chunk f = hvc::stft_chunk(pix, cplx, set, w, s, nwin);
                 CHECK(f.windows == f.least && (f.windows == 1 || (long)(f.windows - 1) * s + w <= set));
               }
+              // host frames: the larger chunks only where the smaller share over a quarter
+              const hvc::Chunk h = hvc::stft_chunk(pix, cplx, 0, w, s, nwin, true);
+              const long shared = s < w ? w - s : 0;
+              CHECK(h.windows <= nwin && h.least <= h.windows);
+              CHECK(h.windows == c.windows || (h.windows == h.least && 4 * shared <= (long)h.windows * s));
+              CHECK(h.windows >= c.windows || h.least == h.windows);
               // memory for chunks of `room` windows
               for (int room : {0, c.least, c.windows - 1, c.windows}) {
                 hvc::Chunk d = c;
