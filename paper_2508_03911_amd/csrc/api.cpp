@@ -566,7 +566,7 @@ static SpatialBytes spatial_bytes(int in_t, int ny, int nx, const hv_optics& o, 
 static hv_status stft_chunks(Ctx* c, hipStream_t st, bool second, const SpatialBytes& b, int ny, int nx, bool mixed,
                              int w, int stride, int nwin, hvc::Chunk* chunk, Ctx::Lane2** l2) {
   *l2 = nullptr;
-  *chunk = hvc::stft_chunk((long)ny * nx, mixed ? 4 : 8, c->chunk_frames, w, stride, nwin);
+  *chunk = hvc::stft_chunk((long)ny * nx, mixed ? 4 : 8, b.slot[1] != 0, c->chunk_frames, w, stride, nwin);
   return hvc::with_room(*chunk, HV_ERR_NOMEM, [&](int g) -> hv_status {
     hv_status s = HV_OK;
     hipStream_t streams[2] = {st, nullptr};
@@ -1153,7 +1153,8 @@ hv_status hv_stft_moments_host(hv_ctx* ctx, const void* host_in, int in_t, int n
   void* in_dev[2];
   float* out_dev[2][3];
   Ctx::Lane2* l2 = nullptr;
-  hvc::Chunk chunk = hvc::stft_chunk((long)frame, mixed ? 4 : 8, ctx->chunk_frames, w, stride, nwin_total, true);
+  hvc::Chunk chunk = hvc::stft_chunk((long)frame, mixed ? 4 : 8, optics->method == HV_AS, ctx->chunk_frames, w, stride,
+                                     nwin_total, true);
   if ((s = hvc::with_room(chunk, HV_ERR_NOMEM, [&](int g) -> hv_status {
          hv_status e = stage(g, st, &in_dev[0], out_dev[0]);
          if (e == HV_OK && nwin_total > g) {

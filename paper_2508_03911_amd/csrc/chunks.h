@@ -29,7 +29,13 @@ struct Chunk {
 // 1097 -> 884, 384^2 W 64 stride 16 6266 -> 2213, 256^2 W 32 stride 8 1039 -> 962;
 // fp16 916 -> 743, 2505 -> 1768, 839 -> 787).  Without overlap the size of
 // auto_frames, but no more than its 96 MiB where that is 32 frames or more (512^2
-// FP32, 64 -> 32 frames: 1711 -> 1512; smaller launches lose at larger frames).
+// FP32, 64 -> 32 frames: 1711 -> 1512; smaller launches lose at larger frames), in
+// whole windows: for the angular spectrum the nearest number, for Fresnel no more
+// than fit (about 2^27 pixels of frames, us, with one window of 32 frames and with two:
+// angular spectrum, rows x columns, 320x512 794 and 679, 384^2 1235 and 1191, 1280x128
+// 1043 and 996, 128x1280 1355 and 1384, 1280x256 mixed 871 and 824, where 51 to 57
+// frames fit; 384x512 785 and 756, 256x800 1254 and 1283, where 40 to 43 fit; Fresnel
+// 320x512 875 and 920, 384^2 1041 and 1016, 1280x128 875 and 988).
 // set_frames: the caller's frames per chunk (0: automatic).
 //
 // uploaded: frames from host memory, whose chunks are copied in and out beside the
@@ -40,12 +46,17 @@ struct Chunk {
 // 8,269 and 8,375 to 10,200, 2048 of stride 8 6,167 to 6,227 and 6,930, but 512 of
 // stride 16 1,360 and 1,288; 211 of 1024x512 stride 16, a third shared, 7,086 and
 // 6,430, 1024 of 384^2 W 64 stride 16, 48 frames for 16 new ones, 13,500 and 6,830).
-inline Chunk stft_chunk(long pix, int cplx, int set_frames, int w, int stride, int nwin, bool uploaded = false) {
+inline Chunk stft_chunk(long pix, int cplx, bool as, int set_frames, int w, int stride, int nwin,
+                        bool uploaded = false) {
   const long per = pix * cplx * 3 / 2;
   long f = set_frames > 0 ? set_frames : auto_frames(pix, cplx);
   if (set_frames <= 0 && (96L << 20) / per >= 32) f = std::min(f, (96L << 20) / per);
   auto windows = [&](long frames) { return frames >= w ? (frames - w) / stride + 1 : 1L; };
-  const long least = std::min<long>(windows(f), nwin);
+  long least = windows(f);
+  // one window more where that is nearer to f, and no more than the 64 frames of auto_frames
+  const long more = least * stride + w;
+  if (as && set_frames <= 0 && stride >= w && f < 64 && more <= 64 && 2 * (more - f) < stride) ++least;
+  least = std::min<long>(least, nwin);
   long g = least;
   if (set_frames <= 0 && stride < w && !(uploaded && 4L * (w - stride) <= least * stride)) {
     g = std::max(g, std::min(16L * (w - stride) / stride + 1, windows((1L << 30) / per)));
