@@ -106,19 +106,21 @@ __global__ __launch_bounds__(NTF, (W >= 64 ? 3 : W >= 32 ? 4 : 6)) void k_field(
         if (g.mask >> k & 1) dst[g.index[k] * npix] = c2::scale(x[k], g.amp);
     }
     if (!g.out[0] && !g.out[1] && !g.out[2]) return;
-    float e0 = 0.f, e1 = 0.f, e2 = 0.f;
+    // four partial sums, bin 0, the largest, last: one chain of 30 bins loses twice as
+    // much to rounding
+    float e[3][4] = {};
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
+    for (int k = W - 1; k >= 0; --k) {
       if (g.mask >> k & 1) {
         const float pw = x[k].x * x[k].x + x[k].y * x[k].y;
-        e0 += pw;
-        e1 += g.wk[k] * pw;
-        e2 += g.wk[W + k] * pw;
+        e[0][k & 3] += pw;
+        e[1][k & 3] += g.wk[k] * pw;
+        e[2][k & 3] += g.wk[W + k] * pw;
       }
     }
-    if (g.out[0]) g.out[0][o] = e0 * a2;
-    if (g.out[1]) g.out[1][o] = e1 * a2;
-    if (g.out[2]) g.out[2][o] = e2 * a2;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (g.out[i]) g.out[i][o] = ((e[i][0] + e[i][1]) + (e[i][2] + e[i][3])) * a2;
   } else if constexpr (MODE == ENERGY_LEFT) {
     take_out<W>(x, g, jj);
     float e[4] = {};
@@ -126,12 +128,14 @@ __global__ __launch_bounds__(NTF, (W >= 64 ? 3 : W >= 32 ? 4 : 6)) void k_field(
     for (int t = 0; t < W; ++t) e[t & 3] += x[t].x * x[t].x + x[t].y * x[t].y;
     g.out[0][o] = ((e[0] + e[1]) + (e[2] + e[3])) * a2;
   } else {
-    float e = 0.f;
+    float e = 0.f, e1 = 0.f;  // of every other component
     for (int c = g.c1; c <= g.c2; ++c) {
       const float2 y = dot<W>(x, g.vec + (jj * W + c) * W);
-      e += y.x * y.x + y.y * y.y;
+      const float t = e1;
+      e1 = e + (y.x * y.x + y.y * y.y);
+      e = t;
     }
-    g.out[0][o] = e * a2;
+    g.out[0][o] = (e + e1) * a2;
   }
 }
 

@@ -141,18 +141,24 @@ __global__ __launch_bounds__((BandShape<NX, ROWS>::NT), (W >= 64 || NX == 800 ||
       for (int b = 0; b < g.nb; ++b) dst[b * npix] = c2::scale(col[b * (ROWS * S)], g.amp);
     }
     if (!images) continue;
-    float e0 = 0.f, e1 = 0.f, e2 = 0.f;
-#pragma unroll 4
-    for (int b = 0; b < g.nb; ++b) {
+    // four partial sums, bin 0, the largest, last: one chain of 30 bins loses twice as
+    // much to rounding
+    float m[3][4] = {};
+    auto add = [&](int b, int i) {
       const float2 v = col[b * (ROWS * S)];
       const float pw = v.x * v.x + v.y * v.y;
-      e0 += pw;
-      e1 += f1[b] * pw;
-      e2 += f2[b] * pw;
-    }
-    if (g.out[0]) g.out[0][o + e] = e0 * a2;
-    if (g.out[1]) g.out[1][o + e] = e1 * a2;
-    if (g.out[2]) g.out[2][o + e] = e2 * a2;
+      m[0][i] += pw;
+      m[1][i] += f1[b] * pw;
+      m[2][i] += f2[b] * pw;
+    };
+    int b = g.nb;
+    while (b & 3) add(--b, 0);
+    for (; b > 0; b -= 4)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) add(b - 1 - i, i);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (g.out[i]) g.out[i][o + e] = ((m[i][0] + m[i][1]) + (m[i][2] + m[i][3])) * a2;
   }
 }
 
