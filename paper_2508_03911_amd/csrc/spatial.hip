@@ -550,27 +550,34 @@ constexpr int p2floor(int r) {
   return p;
 }
 
-// Calls of few 256-wide frames leave CUs without a 64-row tile; they take 16 rows
-// (8 frames of 256^2 8.9 -> 6.6 us with the event pair that times it, 32 frames 9.2
-// -> 7.7, 64 frames or 256 tiles 10.6/10.9).  Both give the same bits.
+// Calls of few frames leave CUs without a tile: below one tile a CU they take tiles
+// of a quarter of the rows, of half for the widths that have 32 rows or fewer.  us
+// with the event pair that times it, full and small tiles, FP32 (fp16 storage gains as
+// much): 32 frames of 128^2 6.8 and 6.5, 64 (128 tiles) 7.7 and 7.2, 128 (256 tiles)
+// 9.6 and 9.5; 1 frame of 256^2 7.1 and 6.3, 32 (128 tiles) 8.9 and 7.9, 64 10.3 and
+// 10.1, 128 13.2 and 13.9; 1 of 512^2 8.0 and 6.6, 8 (128 tiles) 9.8 and 8.3; 1 of
+// 1024^2 (64 tiles) 9.8 and 8.6, 8 of fp16 (512 tiles) 13.8 and 15.7.  Frames 64 wide
+// have no smaller tile that splits over the threads but a half, which gains nothing
+// (64 frames 6.2 and 6.3).  Both give the same bits.
 template <int NX, typename TIN, typename TOUT, int DIV = 1>
 void go_r2c(const void* in, void* out, int n, int ny, float scale, hipStream_t st) {
   constexpr int ROWS = cap64(16384 / NX) / DIV;
   const int nunits = n * (ny / ROWS);
-  if constexpr (NX == 256 && DIV == 1)
-    if (nunits < 256) return go_r2c<NX, TIN, TOUT, 4>(in, out, n, ny, scale, st);
+  if constexpr (NX > 64 && DIV == 1)
+    if (nunits < 256) return go_r2c<NX, TIN, TOUT, (NX < 512 ? 4 : 2)>(in, out, n, ny, scale, st);
   auto kern = k_row_r2c<NX, ROWS, TIN, TOUT>;
   hipLaunchKernelGGL(kern, dim3(persistent_grid(kern, NT, nunits)), dim3(NT), 0, st, (const TIN*)in, (TOUT*)out, ny,
                      nunits, scale);
 }
 
-// Columns per tile: 16 of an FP32 frame 128 high, which fills the CUs sooner (whole
-// moments of 128 frames of 128^2 28.2 -> 28.6 us against 8 columns where that is best,
-// 32 columns 32.1; of 16384 frames 1245 us against 1337 of 8 and 1314 of 32).  The number of
-// frames does not enter: another tile's last bits differ, and a frame's bits must
-// not depend on its company.  fp16 storage, which would carry a last-bit
-// difference on, keeps 32, and a frame 64 high has no gain (512 wide: 635 us against 666).
-// Eight of the heights 320 and 384, whose columns have to split over the threads.
+// Columns per tile: 32 of a frame up to 128 high, fewer of taller ones, and 16 of an
+// FP32 frame 128 high, the best over all numbers of frames (whole moments of 128^2
+// frames, us, with 8, 16 and 32 columns: 128 frames 28.2, 28.6 and 32.1, 16384 frames
+// 1337, 1245 and 1314).  The number of frames does not enter: another tile's last
+// bits differ, and a frame's bits must not depend on its company.  fp16 storage, which
+// would carry a last-bit difference on, keeps 32, and a frame 64 high gains nothing
+// (512 wide, 16 columns for 32: 635 -> 666 us).  Eight of the heights 320 and 384,
+// whose columns have to split over the threads.
 template <int NY, typename TIO>
 void go_col_as(const void* in, void* out, const float2* hs, int n, int nx, hipStream_t st) {
   constexpr int BC =  // divides nx/2 >= 32
@@ -632,9 +639,8 @@ hv_status launched(const char* what) {
   return HV_OK;
 }
 
-// Calls F<N>(args...) for N in {64, 128, 256, 512, 1024} (the real-input
-// row pass, the column pass of the angular spectrum and the fused temporal
-// kernel, which rely on power-of-two sides).
+// Calls F<N>(args...) for N in {64, 128, 256, 512, 1024}: the real-input row pass and
+// the column pass of the angular spectrum (which also takes heights 320 and 384 in FP32).
 #define HV_SWITCH_N(n, CALL)          \
   switch (n) {                        \
     case 64: { constexpr int N_ = 64; CALL; } break;     \
