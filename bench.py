@@ -44,7 +44,7 @@ def bytes_per_pxf(prec: int, nb: int) -> dict:
 
 # library sources that build the kernels and launch shapes of this workload
 # (the counter summary under profiles/ is tied to them)
-PROFILED_SOURCES = ("api.cpp", "band.hip", "fft_lds.h", "field.hip", "gmem.h", "hv_ctx.h", "hv_internal.h",
+PROFILED_SOURCES = ("api.cpp", "band.hip", "chunks.h", "fft_lds.h", "field.hip", "gmem.h", "hv_ctx.h", "hv_internal.h",
                     "reg_fft.h", "rowband.hip", "spatial.hip", "temporal.hip")
 
 
@@ -427,9 +427,11 @@ def precision_case(hv, torch, steps):
     nb = len(hv.band_bins(tp)[0])
     nwin = n // w
     npix = ny * nx
-    # useful flops per pixel and window of the GEMM (real arithmetic on
-    # (re, im)-interleaved operands, K = 2W)
-    flops = {"gram": 2 * (2 * w) ** 2}
+    # flops per pixel and window of the GEMM (real arithmetic on
+    # (re, im)-interleaved operands, K = 2W): the 32 x 32 tiles that the kernel
+    # forms, those on and above the diagonal of a symmetric matrix
+    tiles = 2 * w // 32
+    flops = {"gram": 2 * 32 * 32 * (tiles * (tiles + 1) // 2)}
     ctx = hv.Context(0)
     out = {"workload": f"{n} uint16 frames of {nx}x{ny} (12-bit), Fresnel z={spec.z} m, W={w} stride {w}, "
                        f"{nb} band bins, PCA components 1..63", "frames": n}

@@ -155,10 +155,16 @@ hv_status hv_ctx_set_stft_order(hv_ctx* ctx, int order);
  * Turning it on or off clears the totals. */
 hv_status hv_ctx_set_timing(hv_ctx* ctx, int on);
 /* Waits for the recorded launches and returns the total milliseconds and the
- * launch count of kernel `name` ("row_r2c", "col_as", "rowinv_coef",
- * "row_inv", "field_coef", "rows_c2c", "col_full", "fresnel_rows",
- * "fresnel_cols", "band_rows", "band_cols", "band_power", "gram", "jacobi",
- * "proj_energy"). */
+ * launch count of kernel `name`:
+ *   "row_r2c", "col_as"   rows and columns of real frames, angular spectrum;
+ *   "rows_c2c", "col_full" the same of complex rows and every column;
+ *   "row_inv"             inverse rows to the field;
+ *   "rowinv_coef"         temporal transform and inverse rows of the band's bins
+ *                         in one kernel, with the moments;
+ *   "field_coef"          temporal transform of a field in memory, with the moments;
+ *   "fresnel_rows", "fresnel_cols"; "band_rows", "band_cols", "band_power" (band
+ *   first); "time_fft" (volume);
+ *   "gram", "jacobi" (rotations and eigenvectors), "proj_energy", "ssa_moments". */
 hv_status hv_ctx_kernel_time(hv_ctx* ctx, const char* name, double* total_ms, long* launches);
 
 /* ---------------------------------------------------------------- spatial */
@@ -220,7 +226,7 @@ hv_status hv_stft_moments(hv_ctx* ctx, const void* in, int in_t, int n, int ny, 
  *   - it always takes the per-frame order on hip_stream alone, in chunks of
  *     as many windows as the scratch holds;
  *   - a shape whose single window needs more than 256 MiB of workspace
- *     (ny*nx*W*(1.5 or 2)*(8 FP32 or 4 mixed) bytes; 1024 x 1024 FP32 at
+ *     (ny*nx*W*(1.5 to 3)*(8 FP32 or 4 mixed) bytes; 1024 x 1024 FP32 at
  *     W = 32 is one) returns HV_ERR_SHAPE.
  * Every call on one GPU shares that GPU's scratch: calls that overlap on one
  * GPU (two host threads, or two streams whose work overlaps) race and
@@ -292,11 +298,11 @@ hv_status hv_pca(hv_ctx* ctx, const void* in, int in_t, int n, int ny, int nx, c
  * hv_stft_moments: S_k = sum_t X_f[:, t] exp(-2 pi i k t / W), with
  * M_n = sum_{k in band} f_k^n |S_k|^2 over the band of `temporal` (window
  * W = temporal->window in {16, 32, 64}, stride temporal->stride).  The
- * components (few of them, or the few left out) are summed and put into or
- * taken out of each pixel's samples ahead of the DFT; for other ranges the
- * projection, the back-projection and the DFT are folded into one set of
- * coefficients per window (FP64-built) for a GEMM.  Either way the field is
- * read once after the Gram GEMM.
+ * components left out, where they are few, are taken out of each pixel's
+ * samples ahead of the DFT; for other ranges the projection, the
+ * back-projection and the DFT are folded into one set of coefficients per
+ * window (FP64-built) for a GEMM.  Either way the field is read once after
+ * the Gram GEMM.
  *   in       frames (HV_U8/HV_U16 with optics) or field (HV_C64, optics NULL)
  *   m0..m2   [J][ny][nx] float32 (nullable, not all)
  *   eigvals  [J][W] float64 (nullable), offdiag [J] (nullable) as in hv_pca
