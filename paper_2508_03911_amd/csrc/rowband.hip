@@ -144,18 +144,25 @@ __global__ __launch_bounds__((BandShape<NX, ROWS>::NT), (W >= 64 || NX == 800 ||
     // four partial sums, bin 0, the largest, last: one chain of 30 bins loses twice as
     // much to rounding
     float m[3][4] = {};
-    auto add = [&](int b, int i) {
-      const float2 v = col[b * (ROWS * S)];
+    auto add = [&](int i, float2 v, float w1, float w2) {
       const float pw = v.x * v.x + v.y * v.y;
       m[0][i] += pw;
-      m[1][i] += f1[b] * pw;
-      m[2][i] += f2[b] * pw;
+      m[1][i] += w1 * pw;
+      m[2][i] += w2 * pw;
     };
     int b = g.nb;
-    while (b & 3) add(--b, 0);
-    for (; b > 0; b -= 4)
+#pragma unroll 1
+    while (b & 3) {
+      --b;
+      add(0, col[b * (ROWS * S)], f1[b], f2[b]);
+    }
+#pragma unroll 1  // unrolled further, the weights come in pieces that are waited for one by one
+    while (b > 0) {
+      b -= 4;
+      const float2* c = col + b * (ROWS * S);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) add(b - 1 - i, i);
+      for (int i = 0; i < 4; ++i) add(i, c[i * (ROWS * S)], f1[b + i], f2[b + i]);
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
       if (g.out[i]) g.out[i][o + e] = ((m[i][0] + m[i][1]) + (m[i][2] + m[i][3])) * a2;
