@@ -575,10 +575,12 @@ static hv_status stft_chunks(Ctx* c, hipStream_t st, bool second, const SpatialB
       if (!(*l2 = c->lane2(st, &s))) return s;
       streams[n++] = (*l2)->s;
     }
-    const size_t nf = (size_t)(g - 1) * stride + w;
-    for (int i = 0; i < n; ++i)
+    for (int i = 0; i < n; ++i) {
+      const int windows = i == 0 ? std::min(g, nwin) : std::min(g, nwin - g);  // of its largest chunk
+      const size_t nf = (size_t)(windows - 1) * stride + w;
       for (int slot = 0; slot < 3; ++slot)
         if (s == HV_OK && b.slot[slot]) s = c->work(streams[i], slot).ensure(nf * b.slot[slot], &c->held);
+    }
     if (s == HV_ERR_NOMEM)
       for (int i = 0; i < n; ++i)
         for (int slot = 0; slot < 3; ++slot) c->work(streams[i], slot).drop(&c->held);
